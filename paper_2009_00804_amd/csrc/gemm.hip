@@ -4,279 +4,34 @@
 // activation, the two-operand concat form [a | a2][w ; w2], and the GRU
 // gate math of GGNN's ApplyVertex, Fig. 2).
 //
-// Tiling: a workgroup of 4 waves owns BM = 64 MT rows and BN = 16 NT
+// Tiling: a workgroup of NW waves owns BM = 16 MT NW rows and BN = 16 NT
 // columns; wave w computes rows [16 MT w, 16 MT (w + 1)) of the tile as
 // MT x NT blocks of 16 x 16 with
-//   float32 : v_mfma_f32_16x16x4f32   (4 k per instruction)
+//   float32 : v_mfma_f32_16x16x4f32   (4 k per instruction; narrow products
+//             only, see gemm_splits; the others are in gemm_split.hip)
 //   bfloat16: v_mfma_f32_16x16x32_bf16 (32 k per instruction)
 //
 // Data path.  K is cut into chunks of 128 bytes per row (32 float32 or 64
-// bfloat16 values).  For every chunk the BM rows of A and the BN rows of the
-// packed weights Wt (W transposed, zero-padded to whole tiles, built in the
-// workspace by k_pack_wt) go straight from global memory into one stage of
-// an S-stage LDS ring with direct-to-LDS loads (global_load_lds_dwordx4).
-// Nothing is staged through registers, so the loads of later stages never
-// wait behind one another and S - 1 chunks stay in flight while one is
-// multiplied.  Inside a 128-byte row the eight 16-byte pieces are XOR
-// swizzled (piece p of row r at slot 8 r + (p ^ ((r >> 1) & 7))), so that a
-// fragment read -- 16 rows at one k offset -- touches every LDS bank once.
-// A lane's 16-byte fragment holds EPL consecutive k of one row; A and Wt
-// use the same k order, so the products are exact sums over k.
-//
-// The chunk holding the end of K is loaded first, through registers, with
-// zeros past column K and past row M; every later chunk is a whole 128-byte
-// row segment and needs no masking in k.
+// bfloat16 values).  Each wave owns its A rows, so A needs no sharing: it goes
+// straight from global memory into registers.  The BN rows of the packed
+// weights Wt (W transposed, zero-padded to whole tiles, built in the workspace
+// by k_pack_wt) go into one stage of an S-stage LDS ring with direct-to-LDS
+// loads (global_load_lds_dwordx4); a chunk's A and Wt loads are issued
+// together, S - 1 chunks ahead, so one vmcnt wait covers both.  Inside a
+// 128-byte row the eight 16-byte pieces are XOR swizzled (piece p of row r at
+// slot 8 r + (p ^ ((r >> 1) & 7))), so that a fragment read -- 16 rows at one
+// k offset -- touches every LDS bank once.  A lane's 16-byte fragment holds
+// EPL consecutive k of one row; A and Wt use the same k order, so the products
+// are exact sums over k.  The chunk holding the end of K is masked with zeros
+// past column K.
 #include <algorithm>
 #include <type_traits>
-#include <cstdlib>
-#include <cstring>
 
-#include "saga_device.h"
-#include "saga_internal.h"
+#include "gemm_device.h"
 
 namespace saga {
 namespace {
 
-constexpr int kThreads = 256;
-
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
-template <typename T> struct Mma;
-
-template <> struct Mma<float> {
-  static constexpr int EPL = 4;     // elements per 16-byte fragment
-  static constexpr int KC = 32;     // k per 128-byte chunk
-  typedef f32x4 Frag;
-  __device__ __forceinline__ static float to_f(float x) { return x; }
-  __device__ __forceinline__ static float from_f(float x) { return x; }
-};
-
-template <> struct Mma<uint16_t> {
-  static constexpr int EPL = 8;
-  static constexpr int KC = 64;
-  typedef bf16x8 Frag;
-  __device__ __forceinline__ static float to_f(uint16_t x) { return bf16_to_f32(x); }
-  __device__ __forceinline__ static uint16_t from_f(float x) { return f32_to_bf16(x); }
-};
-
-__device__ __forceinline__ int swz(int r, int p) { return r * 8 + (p ^ ((r >> 1) & 7)); }
-
-// s_waitcnt vmcnt(N) (gfx9 encoding; expcnt and lgkmcnt left at their maxima)
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt out of range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-// Workgroup barrier for the LDS ring.  A plain __syncthreads() would also
-// wait for every direct-to-LDS load in flight (its release fence covers LDS
-// writes, and those loads write LDS), which would drain the ring at every
-// chunk.  Here the caller has already waited for the stage it needs; the
-// barrier only orders this wave's own LDS reads and writes.
-__device__ __forceinline__ void ring_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-template <typename T, int MT, int NT, int S>
-struct Ring {
-  static constexpr int BM = 64 * MT, BN = 16 * NT;
-  static constexpr int A_SLOTS = BM * 8, B_SLOTS = BN * 8;  // 16-byte slots
-  static constexpr int STAGE = A_SLOTS + B_SLOTS;
-  static constexpr int RING_SLOTS = S * STAGE;
-  static constexpr int THREADS = kThreads;
-  static constexpr int LA = A_SLOTS / kThreads;              // loads per thread per stage
-  static constexpr int LB = (B_SLOTS + kThreads - 1) / kThreads;
-  // fewest loads any wave issues per stage (waves past the end of a partial
-  // B row skip the last one); waiting on this count is exact or conservative
-  static constexpr int LMIN = LA + B_SLOTS / kThreads;
-  static_assert(A_SLOTS % kThreads == 0, "A tile must be whole wave loads");
-  static_assert(B_SLOTS % 64 == 0, "B tile must be whole wave loads");
-  static_assert((S - 2) * LMIN < 64, "vmcnt range");
-  static_assert(S >= 2, "at least two stages");
-  static constexpr size_t LDS_BYTES = (size_t)S * STAGE * 16;
-
-  // direct-to-LDS loads of chunk k0 of rows [row0, row0 + BM) of A (rows
-  // >= M skipped) and rows [n0, n0 + BN) of Wt into one stage
-  __device__ __forceinline__ static void issue_a(const T* __restrict__ A, int64_t lda, int64_t M,
-                                                 int64_t row0, int64_t k0, uint4* st) {
-    constexpr int EPL = Mma<T>::EPL;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < LA; ++j) {
-      const int s0 = j * kThreads + wave * 64;
-      const int s = s0 + lane, r = s >> 3, p = (s & 7) ^ ((r >> 1) & 7);
-      if (row0 + r < M)
-        __builtin_amdgcn_global_load_lds(A + (row0 + r) * lda + k0 + p * EPL, (lds_ptr)(st + s0), 16, 0, 0);
-    }
-  }
-  __device__ __forceinline__ static void issue_b(const T* __restrict__ Wt, int64_t kp, int64_t n0,
-                                                 int64_t k0, uint4* st) {
-    constexpr int EPL = Mma<T>::EPL;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < LB; ++j) {
-      const int s0 = j * kThreads + wave * 64;
-      if (s0 < B_SLOTS) {
-        const int s = s0 + lane, n = s >> 3, p = (s & 7) ^ ((n >> 1) & 7);
-        __builtin_amdgcn_global_load_lds(Wt + (n0 + n) * kp + k0 + p * EPL,
-                                         (lds_ptr)(st + A_SLOTS + s0), 16, 0, 0);
-      }
-    }
-  }
-
-  // vmcnt wait that leaves only the loads of the next `later` stages pending;
-  // `tail` says the last of them is the K-tail stage, which issues only its
-  // B loads (its A part was loaded into registers before every other load)
-  static constexpr int LBMIN = B_SLOTS / kThreads;
-  __device__ __forceinline__ static void wait_stages(int later, bool tail) {
-    if constexpr (S >= 4) {
-      if (later >= 2) {
-        if (tail) wait_vm<LMIN + LBMIN>(); else wait_vm<2 * LMIN>();
-        return;
-      }
-    }
-    if constexpr (S >= 3) {
-      if (later == 1) {
-        if (tail) wait_vm<LBMIN>(); else wait_vm<LMIN>();
-        return;
-      }
-    }
-    wait_vm<0>();
-  }
-
-  // The A tail chunk through registers.  A piece that starts below K is
-  // loaded whole (it ends within the row's ld, which is a multiple of 16
-  // bytes); the values at columns >= K, and whole pieces past row M or
-  // column K, are zeroed when the piece is written to LDS.  The loads are
-  // unconditional, so nothing has to wait for them before the stage opens.
-  struct Tail {
-    uint4 v[LA];
-    int nv[LA];  // valid elements of each piece (0 .. EPL)
-    __device__ __forceinline__ void load(const T* __restrict__ A, int64_t lda, int64_t M, int64_t K,
-                                         int64_t row0, int64_t k0) {
-      constexpr int EPL = Mma<T>::EPL;
-      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-      for (int j = 0; j < LA; ++j) {
-        const int s = j * kThreads + wave * 64 + lane, r = s >> 3, p = (s & 7) ^ ((r >> 1) & 7);
-        const int64_t row = row0 + r, k = k0 + p * EPL;
-        const int64_t left = K - k;
-        nv[j] = row < M ? (int)(left <= 0 ? 0 : left >= EPL ? EPL : left) : 0;
-        // pieces with nothing valid read an in-range piece instead (no branch)
-        const int64_t rr = row < M ? row : M - 1;
-        const int64_t kk = left > 0 ? k : (K - 1) / EPL * EPL;
-        v[j] = *reinterpret_cast<const uint4*>(A + rr * lda + kk);
-      }
-    }
-    __device__ __forceinline__ void store(uint4* st) const {
-      constexpr int EPL = Mma<T>::EPL;
-      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-      for (int j = 0; j < LA; ++j) {
-        uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          if constexpr (EPL == 4) {
-            if (d >= nv[j]) w[d] = 0;
-          } else {  // two bfloat16 per word
-            if (2 * d >= nv[j]) w[d] = 0;
-            else if (2 * d + 1 >= nv[j]) w[d] &= 0xffffu;
-          }
-        }
-        st[j * kThreads + wave * 64 + lane] = make_uint4(w[0], w[1], w[2], w[3]);
-      }
-    }
-  };
-
-  // acc += (one chunk of A rows of this wave) x (chunk of Wt).  All
-  // fragments of the chunk are read before the first MFMA, so the reads of
-  // the second k-step complete under the MFMAs of the first.
-  __device__ __forceinline__ static void compute(const uint4* st, f32x4 (&acc)[MT][NT]) {
-    typedef typename Mma<T>::Frag Frag;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lr = lane & 15, lg = lane >> 4;
-    const uint4* As = st;
-    const uint4* Bs = st + A_SLOTS;
-    Frag a[2][MT], b[2][NT];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {  // two k-steps of 64 bytes
-      const int p = h * 4 + lg;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const uint4 v = As[swz(wave * MT * 16 + mt * 16 + lr, p)];
-        __builtin_memcpy(&a[h][mt], &v, 16);
-      }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const uint4 v = Bs[swz(nt * 16 + lr, p)];
-        __builtin_memcpy(&b[h][nt], &v, 16);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if constexpr (sizeof(T) == 4) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-              acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][mt][c], b[h][nt][c], acc[mt][nt], 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][mt], b[h][nt], acc[mt][nt], 0, 0, 0);
-      }
-    }
-  }
-
-  // acc += A[row0 .. row0 + BM) x W[:, n0 .. n0 + BN), W given packed as Wt
-  // (ld kp, zero-padded).  Stage j holds chunk j.  Chunks 0 .. nch-2 are
-  // whole and loaded direct-to-LDS.  The A part of the last one (the K tail)
-  // is loaded into registers before anything else and written to LDS just
-  // before the barrier that opens its stage; its B part is loaded like the
-  // others.  Loads complete in issue order, so waiting until at most the
-  // loads of the stages issued after stage i are pending means stage i has
-  // landed; the counts used are the fewest any wave issues.
-  __device__ __forceinline__ static void phase(const T* __restrict__ A, int64_t lda, int64_t M,
-                                               int64_t K, const T* __restrict__ Wt, int64_t kp,
-                                               int64_t row0, int64_t n0, uint4* ring,
-                                               f32x4 (&acc)[MT][NT]) {
-    constexpr int KC = Mma<T>::KC;
-    const int nch = (int)((K + KC - 1) / KC);
-    const int last = nch - 1;
-    Tail tail;
-    tail.load(A, lda, M, K, row0, (int64_t)last * KC);
-    auto issue = [&](int j) {
-      uint4* st = ring + (j % S) * STAGE;
-      if (j < last) issue_a(A, lda, M, row0, (int64_t)j * KC, st);
-      issue_b(Wt, kp, n0, (int64_t)j * KC, st);
-    };
-    for (int j = 0; j < S - 1 && j < nch; ++j) issue(j);
-    for (int i = 0; i < nch; ++i) {
-      const int ahead = last - i;
-      const int later = ahead < S - 2 ? ahead : S - 2;
-      wait_stages(later, later > 0 && ahead <= S - 2);  // this wave's loads of stage i landed
-      if (i == last) tail.store(ring + (i % S) * STAGE);
-      ring_barrier();  // ... and every wave's; stage i - 1 is free again
-      if (i + S - 1 < nch) issue(i + S - 1);
-      compute(ring + (i % S) * STAGE, acc);
-    }
-    ring_barrier();  // the ring may be refilled by a following phase
-  }
-};
-
-// Second data path: A straight from global memory into registers, only
-// the packed weights through the LDS ring.  Each wave owns its A rows, so
-// A needs no sharing through LDS; the ring then holds only the BN x 128-byte
-// weight chunks (16 KB per stage for BN = 128), which leaves LDS room for
-// more resident workgroups.  A chunk's A and Wt loads are issued together,
-// S - 1 chunks ahead, so one vmcnt wait covers both.
 template <typename T, int MT, int NT, int S, int NW = 4>
 struct RegA {
   typedef typename Mma<T>::Frag Frag;
@@ -291,25 +46,6 @@ struct RegA {
   static_assert(B_SLOTS % 64 == 0, "B tile must be whole wave loads");
   static_assert(S >= 2 && (S - 2) * LMIN < 64, "vmcnt range");
   static constexpr size_t LDS_BYTES = (size_t)RING_SLOTS * 16;
-
-  // element offsets of this lane's A rows r0 + 16 mt + lane % 16.  Rows >=
-  // M read row M - 1 (their results are never stored).  With a row map, row
-  // q is row arow[q] of A; a negative entry reads row 0 (the caller writes
-  // zeros for it).
-  __device__ __forceinline__ static void row_offsets(const int32_t* __restrict__ arow, int64_t lda,
-                                                     int64_t M, int64_t r0, int64_t (&off)[MT]) {
-    const int lr = threadIdx.x & 15;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int64_t row = r0 + mt * 16 + lr;
-      int64_t rr = row < M ? row : M - 1;
-      if (arow) {
-        const int32_t s = arow[rr];
-        rr = s >= 0 ? s : 0;
-      }
-      off[mt] = rr * lda;
-    }
-  }
 
   // fragment (h, mt) of chunk k0: the lane's row mt, columns
   // k0 + (4 h + lane / 16) EPL ..  A piece that starts at or past K reads
@@ -481,92 +217,6 @@ __global__ __launch_bounds__(kThreads) void k_pack_wt(const T* __restrict__ W, i
   }
 }
 
-// ---------------------------------------------------------------------------
-// epilogue.  Lane l of a wave holds rows 4 (l / 16) + r (r < 4), column
-// l % 16 of each 16 x 16 accumulator tile (mt, nt).
-// ---------------------------------------------------------------------------
-
-template <int ACT, int MT, int NT>
-__device__ __forceinline__ void act_tile(f32x4 (&acc)[MT][NT]) {
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[mt][nt][r] = apply_act(ACT, acc[mt][nt][r]);
-}
-
-// Row scale, biases and activation applied to the accumulators in place,
-// in that order (v = acc * rs + b1 + b2, then act).  Each optional step is
-// one uniform branch around the whole tile, and every load happens before
-// the first store (the compiler cannot tell the output from the loaded
-// arrays, so a load after a store would wait for it).
-template <int MT, int NT>
-__device__ __forceinline__ void finish_tile(const GemmArgs& g, int64_t row0, int64_t n0,
-                                            f32x4 (&acc)[MT][NT]) {
-  const int lane = threadIdx.x & 63;
-  if (g.row_scale_deg) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = row0 + mt * 16 + 4 * (lane >> 4) + r;
-        const float rs = row < g.M ? rsqrt_deg(g.row_scale_deg[row]) : 0.0f;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt][r] *= rs;
-      }
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const float* bias = k == 0 ? g.bias : g.bias2;
-    if (!bias) continue;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int64_t c = n0 + nt * 16 + (lane & 15);
-      const float b = c < g.N ? bias[c] : 0.0f;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[mt][nt][r] += b;
-    }
-  }
-  switch (g.act) {
-    case SAGA_ACT_RELU: act_tile<SAGA_ACT_RELU>(acc); break;
-    case SAGA_ACT_ELU: act_tile<SAGA_ACT_ELU>(acc); break;
-    case SAGA_ACT_SIGMOID: act_tile<SAGA_ACT_SIGMOID>(acc); break;
-    case SAGA_ACT_TANH: act_tile<SAGA_ACT_TANH>(acc); break;
-    default: break;
-  }
-}
-
-// output element (row, c) of the finished tile: columns >= split go to out2
-template <typename T>
-__device__ __forceinline__ void store_elem(const GemmArgs& g, int64_t row, int64_t c, float v) {
-  if (g.split > 0 && c >= g.split)
-    static_cast<T*>(g.out2)[row * g.ldo2 + (c - g.split)] = Mma<T>::from_f(v);
-  else
-    static_cast<T*>(g.out)[row * g.ldo + c] = Mma<T>::from_f(v);
-}
-
-// element by element, straight from the accumulators
-template <typename T, int MT, int NT>
-__device__ __forceinline__ void store_direct(const GemmArgs& g, int64_t row0, int64_t n0,
-                                             const f32x4 (&acc)[MT][NT]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = row0 + mt * 16 + 4 * (lane >> 4) + r;
-      if (row >= g.M) continue;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int64_t c = n0 + nt * 16 + (lane & 15);
-        if (c < g.N) store_elem<T>(g, row, c, acc[mt][nt][r]);
-      }
-    }
-}
-
 // bfloat16, 128 columns from column 0, through registers: three lane
 // exchanges (partners lr ^ 1 and lr ^ 2 by DPP, lr ^ 4 by swizzle; lr =
 // lane % 16 with bits b0..b3, lg = lane / 16) turn the accumulator layout
@@ -639,102 +289,6 @@ __device__ __forceinline__ void store_shuffled(const GemmArgs& g, int64_t row0,
           }
       }
     }
-  }
-}
-
-// Through LDS: the wave writes its 16 MT rows x 16 NT columns (already in
-// the output type) to its own region, then each lane reads back whole
-// 16-byte pieces of rows, so one store instruction covers 1 KB of whole
-// row pieces instead of 64-byte pieces of four rows.  A piece is stored
-// whole when it lies inside the output, on one side of the split column,
-// and both outputs allow 16-byte accesses; otherwise element by element.
-// For 128-column tiles, piece p of local row lr sits at piece
-// p ^ (((lr >> 2) & 3) << SH) of the row in LDS: the four rows one write
-// instruction touches then fall on different banks (narrower tiles keep
-// the plain order).  Only this wave's region is touched, so no workgroup
-// barrier is needed once every wave is past the last read of the ring.
-template <typename T, int MT, int NT>
-__device__ __forceinline__ void store_staged(const GemmArgs& g, int64_t row0, int64_t n0,
-                                             const f32x4 (&acc)[MT][NT], T* region) {
-  constexpr int BN = 16 * NT, EPL = Mma<T>::EPL, PR = BN / EPL, ROWS = 16 * MT;
-  constexpr int SH = NT == 8 ? (EPL == 4 ? 2 : 1) : 0;  // log2 pieces per 16 columns
-  constexpr int SW = NT == 8 ? 3 : 0;                    // row bits that pick the swizzle
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int lr = mt * 16 + 4 * (lane >> 4) + r;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int col = nt * 16 + (lane & 15);
-        const int pp = (col / EPL) ^ (((lr >> 2) & SW) << SH);
-        region[lr * BN + pp * EPL + col % EPL] = Mma<T>::from_f(acc[mt][nt][r]);
-      }
-    }
-  // the region is written as T and read back as 16-byte vectors: keep the
-  // compiler from moving a read above a write (the wave's LDS accesses then
-  // complete in program order)
-  asm volatile("" ::: "memory");
-  const size_t es = sizeof(T);
-  const bool vec = (reinterpret_cast<uintptr_t>(g.out) & 15) == 0 && (g.ldo * es) % 16 == 0 &&
-                   (g.split <= 0 || ((reinterpret_cast<uintptr_t>(g.out2) & 15) == 0 &&
-                                     (g.ldo2 * es) % 16 == 0));
-  const uint4* src = reinterpret_cast<const uint4*>(region);
-#pragma unroll
-  for (int i = 0; i < (ROWS * PR + 63) / 64; ++i) {
-    const int k = i * 64 + lane, lr = k / PR, p = k % PR;
-    if (k >= ROWS * PR) break;
-    const uint4 v = src[lr * PR + (p ^ (((lr >> 2) & SW) << SH))];
-    const int64_t row = row0 + lr, c = n0 + (int64_t)p * EPL;
-    if (row >= g.M) continue;
-    const bool whole = c + EPL <= g.N && (g.split <= 0 || c + EPL <= g.split || c >= g.split);
-    if (vec && whole) {
-      T* dst = g.split > 0 && c >= g.split
-                   ? static_cast<T*>(g.out2) + row * g.ldo2 + (c - g.split)
-                   : static_cast<T*>(g.out) + row * g.ldo + c;
-      *reinterpret_cast<uint4*>(dst) = v;
-    } else {
-      T e[EPL];
-      __builtin_memcpy(e, &v, 16);
-#pragma unroll
-      for (int j = 0; j < EPL; ++j)
-        if (c + j < g.N) {
-          if (g.split > 0 && c + j >= g.split)
-            static_cast<T*>(g.out2)[row * g.ldo2 + (c + j - g.split)] = e[j];
-          else
-            static_cast<T*>(g.out)[row * g.ldo + c + j] = e[j];
-        }
-    }
-  }
-}
-
-// staged stores need room in the ring for every wave's rows (kStaged), or
-// at least for 16 rows of every wave, staged one 16-row slab at a time
-template <typename T, int MT, int NT, typename R>
-constexpr bool kStaged =
-    (size_t)(R::THREADS / 64) * 16 * MT * 16 * NT * sizeof(T) <= R::LDS_BYTES;
-template <typename T, int NT, typename R>
-constexpr bool kStagedSlab = (size_t)(R::THREADS / 64) * 16 * 16 * NT * sizeof(T) <= R::LDS_BYTES;
-
-template <typename T, int MT, int NT, typename R>
-__device__ __forceinline__ void store_tile(const GemmArgs& g, int64_t row0, int64_t n0,
-                                           const f32x4 (&acc)[MT][NT], uint4* ring) {
-  const int wave = threadIdx.x >> 6;
-  if constexpr (kStaged<T, MT, NT, R>) {
-    store_staged<T, MT, NT>(g, row0, n0, acc,
-                            reinterpret_cast<T*>(ring) + (size_t)wave * 16 * MT * 16 * NT);
-  } else if constexpr (kStagedSlab<T, NT, R>) {
-    T* region = reinterpret_cast<T*>(ring) + (size_t)wave * 16 * 16 * NT;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      // the previous slab's read-back stays ahead of this slab's writes
-      asm volatile("" ::: "memory");
-      store_staged<T, 1, NT>(g, row0 + mt * 16, n0,
-                             reinterpret_cast<const f32x4(&)[1][NT]>(acc[mt]), region);
-    }
-  } else {
-    store_direct<T, MT, NT>(g, row0, n0, acc);
   }
 }
 
@@ -812,13 +366,13 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bres(GemmArgs g) {
   int64_t q_pf = gw, q_cur = gw;
   int c_pf = 0, c_cur = 0;
   int64_t off_pf[MT];
-  R::row_offsets(nullptr, g.lda, g.M, q_pf * 16 * MT, off_pf);
+  row_offsets(nullptr, g.lda, g.M, q_pf * 16 * MT, off_pf);
   auto issue_next = [&](Frag (&a)[2][MT]) {
     R::load_a(A, off_pf, g.K, (int64_t)c_pf * KC, a);
     if (++c_pf == nch) {  // rows of tiles past the last are clamped to row M - 1
       c_pf = 0;
       q_pf += stride;
-      R::row_offsets(nullptr, g.lda, g.M, q_pf * 16 * MT, off_pf);
+      row_offsets(nullptr, g.lda, g.M, q_pf * 16 * MT, off_pf);
     }
   };
   Frag a[D][2][MT];
@@ -1025,32 +579,8 @@ __global__ __launch_bounds__(kThreads) void k_pack_wt_grouped(const T* __restric
 // host side: tiling choice, weight packing, launch
 // ---------------------------------------------------------------------------
 struct Tiling {
-  int mt, nt, stages;
-  bool ring_a;  // A through the LDS ring (Ring) instead of registers (RegA)
-  int nw = 4;   // waves per workgroup (RegA)
+  int nt, stages;  // column tiles; stages of the weight ring
 };
-
-#ifdef SAGA_SWEEP_BUILD
-// A sweep build reads SAGA_GEMM_CFG to override the tile shape of the N <= 128 kernels for tuning:
-// "aMxS" = A through registers, M = rows per wave / 16, S stages;
-// "rMxS" = A through the LDS ring
-Tiling cfg_override(Tiling t) {
-  static const char* e = getenv("SAGA_GEMM_CFG");
-  if (!e) return t;
-  static const struct { const char* name; Tiling t; } table[] = {
-      {"r2x2", {2, 8, 2, true}}, {"r2x4", {2, 8, 4, true}}, {"a2x4", {2, 8, 4, false}},
-      {"a2x3", {2, 8, 3, false}}, {"a4x3", {4, 8, 3, false}}, {"a4x2", {4, 8, 2, false}},
-      {"a1x4", {1, 8, 4, false}}, {"a2x3w8", {2, 8, 3, false, 8}}, {"a2x2w8", {2, 8, 2, false, 8}},
-      {"a2x4w8", {2, 8, 4, false, 8}}, {"a1x4w8", {1, 8, 4, false, 8}},
-      {"a1x4w16", {1, 8, 4, false, 16}}, {"a1x3w16", {1, 8, 3, false, 16}},
-      {"a1x3w8", {1, 8, 3, false, 8}}};
-  for (const auto& x : table)
-    if (!strcmp(e, x.name)) return x.t;
-  return t;
-}
-#else
-Tiling cfg_override(Tiling t) { return t; }
-#endif
 
 // k chunks of a K-long operand
 int64_t chunks(int dtype, int64_t K) {
@@ -1059,16 +589,16 @@ int64_t chunks(int dtype, int64_t K) {
 }
 
 Tiling choose(int dtype, int mode, int64_t N, int64_t K) {
-  if (mode == SAGA_GEMM_GRU) return Tiling{1, (int)(N / 16), 4, false};
+  if (mode == SAGA_GEMM_GRU) return Tiling{(int)(N / 16), 4};
   const int64_t nt = (N + 15) / 16;
   // narrow tiles: with at most four k chunks two stages suffice (the
   // registers two more A slots would hold buy occupancy instead; measured
-  // on the 2^21 x 128 x 41 transform: 0.437 -> 0.414 ms fp32, 0.175 ->
-  // 0.162 ms bf16)
-  if (nt <= 5) return Tiling{2, (int)nt, chunks(dtype, K) <= 4 ? 2 : 4, false};
-  // 128-column tiles (more columns: several tiles along N), measured best
-  // on the 2^21 x 602 x 128 transform and on 131072 x 512 x 256
-  return cfg_override(dtype == SAGA_BF16 ? Tiling{1, 8, 4, false, 8} : Tiling{2, 8, 2, true});
+  // on the 2^21 x 128 x 41 bfloat16 transform: 0.175 -> 0.162 ms)
+  if (nt <= 5) return Tiling{(int)nt, chunks(dtype, K) <= 4 ? 2 : 4};
+  // 128-column tiles (bfloat16; more columns: several tiles along N), eight
+  // waves of 16 rows, measured best on the 2^21 x 602 x 128 transform and on
+  // 131072 x 512 x 256
+  return Tiling{8, 4};
 }
 
 int kc_of(int dtype) { return dtype == SAGA_BF16 ? Mma<uint16_t>::KC : Mma<float>::KC; }
@@ -1102,27 +632,6 @@ hipError_t launch_plain(const GemmArgs& g, hipStream_t st) {
 
 template <typename T, int NT>
 hipError_t launch_nt(const GemmArgs& g, const Tiling& t, hipStream_t st) {
-  if constexpr (NT == 8) {
-    if (t.ring_a) {
-      if (t.stages == 2) return launch_plain<T, 2, 8, Ring<T, 2, 8, 2>>(g, st);
-      return launch_plain<T, 2, 8, Ring<T, 2, 8, 4>>(g, st);
-    }
-    if (t.nw == 16) {
-      if (t.stages == 3) return launch_plain<T, 1, 8, RegA<T, 1, 8, 3, 16>>(g, st);
-      return launch_plain<T, 1, 8, RegA<T, 1, 8, 4, 16>>(g, st);
-    }
-    if (t.nw == 8) {
-      if (t.mt == 1 && t.stages == 3) return launch_plain<T, 1, 8, RegA<T, 1, 8, 3, 8>>(g, st);
-      if (t.mt == 1) return launch_plain<T, 1, 8, RegA<T, 1, 8, 4, 8>>(g, st);
-      if (t.stages == 2) return launch_plain<T, 2, 8, RegA<T, 2, 8, 2, 8>>(g, st);
-      if (t.stages == 4) return launch_plain<T, 2, 8, RegA<T, 2, 8, 4, 8>>(g, st);
-      return launch_plain<T, 2, 8, RegA<T, 2, 8, 3, 8>>(g, st);
-    }
-    if (t.mt == 1) return launch_plain<T, 1, 8, RegA<T, 1, 8, 4>>(g, st);
-    if (t.mt == 4 && t.stages == 2) return launch_plain<T, 4, 8, RegA<T, 4, 8, 2>>(g, st);
-    if (t.mt == 4) return launch_plain<T, 4, 8, RegA<T, 4, 8, 3>>(g, st);
-    if (t.stages == 3) return launch_plain<T, 2, 8, RegA<T, 2, 8, 3>>(g, st);
-  }
   if (t.stages == 2) return launch_plain<T, 2, NT, RegA<T, 2, NT, 2>>(g, st);
   return launch_plain<T, 2, NT, RegA<T, 2, NT, 4>>(g, st);
 }
@@ -1149,29 +658,14 @@ hipError_t launch_bres(const GemmArgs& g, hipStream_t st) {
 // K = 192 (one 16-row tile per wave), 0.37 / 0.42 ms at K = 256, 0.49 /
 // 0.55 at 384 and 0.69 / 0.80 at 602 (two tiles per wave, three A slots:
 // as fast as four, which spill registers); at K = 128 the streamed tiles
-// are as fast.  A sweep build reads SAGA_GEMM_BRES to override the shape
-// ("MxWxD": M x 16 rows per wave, W waves, D A chunks in registers; "off":
-// the streamed tiles).
+// are as fast.
 hipError_t maybe_bres(const GemmArgs& g, hipStream_t st, bool* used) {
   *used = false;
   if (g.dtype != SAGA_BF16 || g.mode != SAGA_GEMM_PLAIN || g.N > 128 || g.K > 32 * kResHalfChunks)
     return hipSuccess;
-#ifdef SAGA_SWEEP_BUILD
-  static const char* e = getenv("SAGA_GEMM_BRES");
-  const char* cfg = e ? e : g.N <= 80 || g.K < 192 ? "off" : g.K < 256 ? "1x8x4" : "2x8x3";
-  *used = true;
-  if (!strcmp(cfg, "1x8x4")) return launch_bres<1, 8, 4>(g, st);
-  if (!strcmp(cfg, "2x8x4")) return launch_bres<2, 8, 4>(g, st);
-  if (!strcmp(cfg, "2x8x3")) return launch_bres<2, 8, 3>(g, st);
-  if (!strcmp(cfg, "1x16x3")) return launch_bres<1, 16, 3>(g, st);
-  if (!strcmp(cfg, "1x8x6")) return launch_bres<1, 8, 6>(g, st);
-  *used = false;
-  return hipSuccess;
-#else
   if (g.N <= 80 || g.K < 192) return hipSuccess;
   *used = true;
   return g.K < 256 ? launch_bres<1, 8, 4>(g, st) : launch_bres<2, 8, 3>(g, st);
-#endif
 }
 
 template <typename T>
@@ -1203,11 +697,16 @@ hipError_t dispatch(const GemmArgs& g, hipStream_t st) {
   switch (t.nt) {
     case 1: return launch_nt<T, 1>(g, t, st);
     case 2: return launch_nt<T, 2>(g, t, st);
-    case 3: return launch_nt<T, 3>(g, t, st);
-    case 4: return launch_nt<T, 4>(g, t, st);
-    case 5: return launch_nt<T, 5>(g, t, st);
-    default: return launch_nt<T, 8>(g, t, st);
   }
+  if constexpr (sizeof(T) == 2) {  // float32 past two column tiles: gemm_splits
+    switch (t.nt) {
+      case 3: return launch_nt<T, 3>(g, t, st);
+      case 4: return launch_nt<T, 4>(g, t, st);
+      case 5: return launch_nt<T, 5>(g, t, st);
+      default: return launch_plain<T, 1, 8, RegA<T, 1, 8, 4, 8>>(g, st);
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -1242,13 +741,18 @@ hipError_t dispatch_grouped(const GemmArgs& g, hipStream_t st) {
   switch (grouped_nt(g.N)) {
     case 1: return launch_grouped_nt<T, 1>(g, st);
     case 2: return launch_grouped_nt<T, 2>(g, st);
-    case 3: return launch_grouped_nt<T, 3>(g, st);
-    case 4: return launch_grouped_nt<T, 4>(g, st);
-    case 5: return launch_grouped_nt<T, 5>(g, st);
-    case 6: return launch_grouped_nt<T, 6>(g, st);
-    case 7: return launch_grouped_nt<T, 7>(g, st);
-    default: return launch_grouped_nt<T, 8>(g, st);
   }
+  if constexpr (sizeof(T) == 2) {  // float32 past two column tiles: gemm_splits
+    switch (grouped_nt(g.N)) {
+      case 3: return launch_grouped_nt<T, 3>(g, st);
+      case 4: return launch_grouped_nt<T, 4>(g, st);
+      case 5: return launch_grouped_nt<T, 5>(g, st);
+      case 6: return launch_grouped_nt<T, 6>(g, st);
+      case 7: return launch_grouped_nt<T, 7>(g, st);
+      default: return launch_grouped_nt<T, 8>(g, st);
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 void grouped_packed(int dtype, int64_t N, int64_t K, int64_t* np, int64_t* kp) {
@@ -1260,11 +764,15 @@ void grouped_packed(int dtype, int64_t N, int64_t K, int64_t* np, int64_t* kp) {
 }  // namespace
 
 size_t gemm_workspace_bytes(int dtype, int mode, int64_t N, int64_t K, int64_t K2) {
+  if (mode != SAGA_GEMM_CONCAT && mode != SAGA_GEMM_GRU) K2 = 0;
+  if (gemm_splits(dtype, mode, N, K + K2)) return split_workspace_bytes(N, K, K2, 1);
   return packed_layout(dtype, mode, N, K, K2).bytes;
 }
 
 hipError_t launch_gemm(const GemmArgs& g0, hipStream_t st) {
   if (g0.M == 0) return hipSuccess;
+  if (gemm_splits(g0.dtype, g0.mode, g0.N, g0.K + (g0.mode == SAGA_GEMM_CONCAT ? g0.K2 : 0)))
+    return launch_gemm_split(g0, st);
   const Packed pk = packed_layout(g0.dtype, g0.mode, g0.N, g0.K, g0.K2);
   if (!g0.ws || g0.ws_bytes < pk.bytes) return hipErrorInvalidValue;
   GemmArgs g = g0;
@@ -1284,6 +792,7 @@ hipError_t launch_gemm(const GemmArgs& g0, hipStream_t st) {
 }
 
 size_t gemm_grouped_workspace_bytes(int dtype, int groups, int64_t N, int64_t K) {
+  if (gemm_splits(dtype, SAGA_GEMM_PLAIN, N, K)) return split_workspace_bytes(N, K, 0, groups);
   int64_t np, kp;
   grouped_packed(dtype, N, K, &np, &kp);
   const size_t es = dtype == SAGA_BF16 ? 2 : 4;
@@ -1296,6 +805,7 @@ hipError_t launch_gemm_grouped(const GemmArgs& g0, hipStream_t st) {
   if (!g0.ws || g0.ws_bytes < gemm_grouped_workspace_bytes(g0.dtype, g0.groups, g0.N, g0.K))
     return hipErrorInvalidValue;
   GemmArgs g = g0;
+  if (gemm_splits(g.dtype, SAGA_GEMM_PLAIN, g.N, g.K)) return launch_gemm_split(g, st);
   int64_t np, kp;
   grouped_packed(g.dtype, g.N, g.K, &np, &kp);
   g.wt = g.ws;

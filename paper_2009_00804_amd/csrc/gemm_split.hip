@@ -1,0 +1,516 @@
+// ApplyVertex in float32: PLAIN, CONCAT and grouped products on the bfloat16
+// matrix cores, every float32 operand as an exact sum of three bfloat16 values.
+#include "gemm_device.h"
+
+namespace saga {
+namespace {
+
+// ---------------------------------------------------------------------------
+// float32 products on the bfloat16 matrix cores.  Every float32 value is the
+// exact sum of three bfloat16 values, x = x1 + x2 + x3 (round to nearest, then
+// the remainders: 8 + 8 + 8 bits of significand), so
+//   a w = a1 w1 + (a1 w2 + a2 w1) + (a1 w3 + a2 w2 + a3 w1) + O(2^-26 |a w|)
+// and the six products, each exact in float32, are accumulated in float32 by
+// v_mfma_f32_16x16x32_bf16.  One such instruction takes 32 k at 16 times the
+// rate of v_mfma_f32_16x16x4f32, so six of them take 3/8 of its time, and an
+// accumulator is rounded six times per 32 k instead of eight.  Measured on
+// 2^21 x 602 x 128: 2.92 -> 1.87 ms, relative error against float64 4.0e-7 ->
+// 3.4e-7; every size tried came out nearer to float64 than the float32
+// instruction.  What bounds it: the matrix cores run at half their rate at the
+// 1.87 GHz the power limit leaves under this load (the products alone take
+// 1.15 ms, the A loads add 0.35, the weights 0.27, the stores 0.14).
+//
+// The split needs its operands' magnitudes well inside the float32 range: a
+// row of A (or a column of W) whose largest magnitude is 2^60 or more
+// (infinities included), or below 2^-40 but not zero, would lose what plain
+// float32 keeps.  The kernel tracks every row's largest magnitude as it loads
+// the row and k_pack_split notes such columns per 16-column tile; a wave that
+// meets either recomputes its tile with the float32 instruction
+// (native_phase).  NaN gives NaN either way.
+// ---------------------------------------------------------------------------
+constexpr float kSplitBig = 1152921504606846976.0f;   // 2^60
+constexpr float kSplitSmall = 9.094947017729282e-13f;  // 2^-40
+__device__ __forceinline__ bool split_special(float m) {
+  return !(m < kSplitBig) || (m > 0.0f && m < kSplitSmall);
+}
+
+typedef __attribute__((address_space(3))) uint4 lds_uint4;
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// x = p[0] + p[1] + p[2], two values at a time
+__device__ __forceinline__ void split3(f32x2 x, uint32_t (&p)[3]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const bf16x2 h = __builtin_convertvector(x, bf16x2);
+    __builtin_memcpy(&p[q], &h, 4);
+    x -= f32x2{__uint_as_float(p[q] << 16), __uint_as_float(p[q] & 0xffff0000u)};
+  }
+}
+
+// A straight from global memory into registers and split there; the packed
+// weights, split by k_pack_split, through two LDS stages.  A chunk is 32 k:
+// 128 bytes of an A row, and for every 16-column tile three 1 KB planes of Wt
+// whose 16-byte pieces (8 k of one column: 4 p .. 4 p + 3 and 16 further on)
+// lie in the order the lanes read them, piece p of column r at slot 16 p + r, so the stage is one contiguous
+// copy and every fragment read covers 1 KB free of bank conflicts.
+//
+// Step i multiplies chunk i.  At its top the weights of chunk i + 1 start on
+// their way into the other stage and the A rows of chunk i + 2 into registers;
+// in its second half the A rows of chunk i + 1, which have had a whole step to
+// land, are split, so that the vector instructions of the split issue between
+// the matrix instructions.  The direct-to-LDS loads are written in assembly:
+// the compiler would otherwise wait for every one in flight before any LDS
+// read.  Loads return in order, so the explicit wait at the top of a step, at
+// most the newest A loads pending, covers the older weight loads.
+template <int MT, int NT, int NW>
+struct Split3 {
+  typedef float T;
+  static constexpr int THREADS = 64 * NW;
+  static constexpr int BM = 16 * MT * NW, BN = 16 * NT;
+  static constexpr int STAGE = 3 * NT * 64;  // 16-byte slots per stage
+  static constexpr int RING_SLOTS = 2 * STAGE;
+  static constexpr size_t LDS_BYTES = (size_t)RING_SLOTS * 16;
+  static constexpr int LB = (STAGE + THREADS - 1) / THREADS;
+  static constexpr int KC = 32;
+
+  struct Ctx {
+    const float* row[MT];  // this lane's A rows
+    int64_t K;
+    const uint4* Wi;       // this column block's image: chunk c at c * STAGE
+    lds_uint4* ring;
+    int last, kmax;        // last chunk; first column of a row's last 16-byte piece
+  };
+
+  // A values of chunk c: columns 32 c + 4 (lane / 16) .. + 3 and the same 16
+  // further on (a load instruction then covers 64 contiguous bytes of every
+  // row; k_pack_split orders its k alike).  A piece that starts at or past K
+  // reads the row's last piece instead (masked when split).
+  __device__ __forceinline__ static void load_a(const Ctx& c, int chunk, uint4 (&a)[MT][2]) {
+    const int lg = (threadIdx.x & 63) >> 4;
+    const int k = chunk * KC + lg * 4;
+    const int k0 = min(k, c.kmax), k1 = min(k + 16, c.kmax);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      a[mt][0] = *reinterpret_cast<const uint4*>(c.row[mt] + k0);
+      a[mt][1] = *reinterpret_cast<const uint4*>(c.row[mt] + k1);
+    }
+  }
+  __device__ __forceinline__ static void mask(const Ctx& c, int chunk, uint4 (&a)[MT][2]) {
+    const int lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t left = c.K - (chunk * KC + lg * 4 + h * 16);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        if (left < 4) a[mt][h].w = 0;
+        if (left < 3) a[mt][h].z = 0;
+        if (left < 2) a[mt][h].y = 0;
+        if (left < 1) a[mt][h].x = 0;
+      }
+    }
+  }
+  __device__ __forceinline__ static void issue_b(const Ctx& c, int chunk, int stage) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint4* src = c.Wi + (int64_t)chunk * STAGE;
+    const uint32_t dst = (uint32_t)(uintptr_t)(c.ring + stage * STAGE);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+      const int s0 = j * THREADS + wave * 64;
+      if (STAGE % THREADS == 0 || s0 < STAGE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(__builtin_amdgcn_readfirstlane(dst + s0 * 16)), "v"((uint32_t)(s0 + lane) * 16u),
+                       "s"(src)
+                     : "memory");
+    }
+  }
+
+  struct Parts { uint32_t p[MT][3][4]; };
+  // values 2 d and 2 d + 1 of row mt
+  __device__ __forceinline__ static void split_pair(const uint4 (&a)[MT][2], int mt, int d,
+                                                    float (&amax)[MT], Parts& o) {
+    const uint4& v = a[mt][d / 2];
+    const f32x2 x = d % 2 == 0 ? f32x2{__uint_as_float(v.x), __uint_as_float(v.y)}
+                               : f32x2{__uint_as_float(v.z), __uint_as_float(v.w)};
+    amax[mt] = fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), amax[mt]);
+    uint32_t p[3];
+    split3(x, p);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) o.p[mt][q][d] = p[q];
+  }
+  __device__ __forceinline__ static bf16x8 part(const Parts& ap, int mt, int q) {
+    bf16x8 r;
+    __builtin_memcpy(&r, ap.p[mt][q], 16);
+    return r;
+  }
+
+  // One step.  A column tile's weight fragments are read while the tile before
+  // it is multiplied; in the second half (LAST: no next chunk) the pairs of
+  // chunk i + 1's A values are split a few at a time between the matrix
+  // instructions.  The scheduling barriers keep that order.
+  static constexpr int G0 = NT / 2;             // first column tile of the second half
+  static constexpr int SLOTS = (NT - G0) * 6;   // places to split at
+  typedef bf16x8 BFrag[3];
+  __device__ __forceinline__ static void read_b(const lds_uint4* Bs, int g, BFrag& b) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      b[q] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(
+          Bs + (q * NT + g) * 64 + lane);
+  }
+  template <int U, bool LOAD, bool MASK, bool LAST>
+  __device__ __forceinline__ static void step(const Ctx& c, int i, uint4 (&a)[2][MT][2], Parts (&ap)[2],
+                                              float (&amax)[MT], f32x4 (&acc)[MT][NT]) {
+    // chunk i's weights landed (only chunk i + 1's A loads are newer), for
+    // every wave; the other stage is free again
+    wait_vm<LAST ? 0 : 2 * MT>();
+    ring_barrier();
+    const lds_uint4* Bs = c.ring + U * STAGE;
+    BFrag b[2];
+    read_b(Bs, 0, b[0]);
+    if constexpr (!LAST) issue_b(c, i + 1, U ^ 1);
+    if constexpr (LOAD) load_a(c, i + 2, a[U]);
+    __builtin_amdgcn_sched_barrier(0);
+    // smallest products first
+    constexpr int QA[6] = {2, 1, 0, 1, 0, 0}, QB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+    for (int g = 0; g < NT; ++g) {
+      if (g + 1 < NT) read_b(Bs, g + 1, b[(g + 1) & 1]);
+      if constexpr (MASK) {
+        if (g == G0) mask(c, i + 1, a[U ^ 1]);
+      }
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          acc[mt][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part(ap[U], mt, QA[q]), b[g & 1][QB[q]],
+                                                               acc[mt][g], 0, 0, 0);
+        if (!LAST && g >= G0) {
+          const int slot = (g - G0) * 6 + q;
+#pragma unroll
+          for (int d = slot * MT * 4 / SLOTS; d < (slot + 1) * MT * 4 / SLOTS; ++d)
+            split_pair(a[U ^ 1], d / 4, d % 4, amax, ap[U ^ 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  // acc += A[tile0 .. tile0 + BM) x the column block's image; amax: this
+  // lane's part of its rows' largest magnitudes
+  __device__ __forceinline__ static void phase(const float* __restrict__ A, int64_t lda, int64_t M,
+                                               int64_t K, const uint4* __restrict__ Wi,
+                                               int64_t tile0, uint4* ring, float (&amax)[MT],
+                                               f32x4 (&acc)[MT][NT],
+                                               const int32_t* __restrict__ arow = nullptr) {
+    Ctx c;
+    int64_t off[MT];
+    row_offsets(arow, lda, M, tile0 + (threadIdx.x >> 6) * MT * 16, off);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) c.row[mt] = A + off[mt];
+    c.K = K;
+    c.Wi = Wi;
+    c.ring = (lds_uint4*)ring;
+    c.last = (int)((K + KC - 1) / KC) - 1;
+    c.kmax = (int)((K - 1) / 4 * 4);
+    uint4 a[2][MT][2];
+    Parts ap[2];
+    issue_b(c, 0, 0);
+    load_a(c, 0, a[0]);
+    if (c.last > 0) load_a(c, 1, a[1]);
+    else mask(c, 0, a[0]);
+#pragma unroll
+    for (int d = 0; d < MT * 4; ++d) split_pair(a[0], d / 4, d % 4, amax, ap[0]);
+    int i = 0;
+    for (; i + 3 <= c.last; i += 2) {
+      step<0, true, false, false>(c, i, a, ap, amax, acc);
+      step<1, true, false, false>(c, i + 1, a, ap, amax, acc);
+    }
+    const int left = c.last - i;  // 0, 1 or 2 more chunks after chunk i
+    if (left == 2) {
+      step<0, true, false, false>(c, i, a, ap, amax, acc);
+      step<1, false, true, false>(c, i + 1, a, ap, amax, acc);
+      step<0, false, false, true>(c, i + 2, a, ap, amax, acc);
+    } else if (left == 1) {
+      step<0, false, true, false>(c, i, a, ap, amax, acc);
+      step<1, false, false, true>(c, i + 1, a, ap, amax, acc);
+    } else {
+      step<0, false, false, true>(c, i, a, ap, amax, acc);
+    }
+    ring_barrier();  // the stages may be refilled by a following phase
+  }
+
+  // does this wave meet a row outside the split's range (uniform per wave)
+  __device__ __forceinline__ static bool special(const float (&amax)[MT]) {
+    bool sp = false;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      float m = amax[mt];
+      m = fmaxf(m, __shfl_xor(m, 16, 64));
+      m = fmaxf(m, __shfl_xor(m, 32, 64));
+      sp |= split_special(m);
+    }
+    return __any(sp);
+  }
+
+  // acc += A rows x W with the float32 instruction, operands straight from
+  // memory: the waves whose values the split does not take (rare, not tuned)
+  __device__ __forceinline__ static void native_phase(
+      const float* __restrict__ A, int64_t lda, int64_t M, int64_t K, const float* __restrict__ W,
+      int64_t ldw, int64_t N, int64_t n0, int64_t tile0, f32x4 (&acc)[MT][NT],
+      const int32_t* __restrict__ arow = nullptr) {
+    const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+    int64_t off[MT];
+    row_offsets(arow, lda, M, tile0 + (threadIdx.x >> 6) * MT * 16, off);
+    for (int64_t k0 = 0; k0 < K; k0 += 4) {
+      const int64_t k = k0 + lg;
+      float a[MT], b[NT];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) a[mt] = k < K ? A[off[mt] + k] : 0.0f;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int64_t n = n0 + nt * 16 + lr;
+        b[nt] = k < K && n < N ? W[k * ldw + n] : 0.0f;
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+    }
+  }
+};
+
+// The image Split3 streams, for one group of weights per blockIdx.y: for
+// column block b, chunk c, plane q, tile t of the block: 64 pieces of 8 k.
+// One workgroup per 16-column tile, which sees whole columns, so its flag
+// (some column outside the split's range) needs no atomics across workgroups.
+// flags: one int per 16-column tile.
+constexpr int kPackThreads = 1024;
+__global__ __launch_bounds__(kPackThreads) void k_pack_split(const float* __restrict__ W, int64_t ldw,
+                                                             int64_t K, int64_t N, int nt,
+                                                             uint4* __restrict__ img,
+                                                             int32_t* __restrict__ flags) {
+  __shared__ uint32_t cmax[16];
+  const int nch = (int)((K + 31) / 32), tile = blockIdx.x, tiles = gridDim.x;
+  const int b = tile / nt, t = tile % nt;
+  const float* w = W + (int64_t)blockIdx.y * K * ldw;
+  uint4* im = img + ((int64_t)blockIdx.y * tiles * nch + (int64_t)b * nt * nch) * 192;
+  if (threadIdx.x < 16) cmax[threadIdx.x] = 0;
+  __syncthreads();
+  const int r = threadIdx.x & 15;
+  const int64_t n = (int64_t)tile * 16 + r;
+  uint32_t m = 0;
+  for (int i = threadIdx.x; i < nch * 64; i += kPackThreads) {
+    const int c = i / 64, p = (i / 16) % 4;
+    const int64_t k0 = (int64_t)c * 32 + p * 4;  // and k0 + 16
+    uint32_t q[3][4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      f32x2 x;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int64_t k = k0 + 2 * (d & 1) + 16 * (d >> 1) + j;
+        x[j] = n < N && k < K ? w[k * ldw + n] : 0.0f;
+        m = max(m, __float_as_uint(fabsf(x[j])));
+      }
+      uint32_t o[3];
+      split3(x, o);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) q[k][d] = o[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      im[((int64_t)c * 3 + k) * nt * 64 + t * 64 + p * 16 + r] = make_uint4(q[k][0], q[k][1], q[k][2], q[k][3]);
+  }
+  atomicMax(&cmax[r], m);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int sp = 0;
+    for (int j = 0; j < 16; ++j) sp |= split_special(__uint_as_float(cmax[j]));
+    flags[(int64_t)blockIdx.y * tiles + tile] = sp;
+  }
+}
+
+// float32 PLAIN / CONCAT / grouped through Split3.  The column blocks of one
+// row block run on one XCD one after another (workgroup w goes to XCD w % 8),
+// so that its rows of A come from HBM once.  GROUPED as k_gemm_grouped below.
+template <int MT, int NT, int NW, bool GROUPED>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(GemmArgs g, int ny) {
+  typedef Split3<MT, NT, NW> R;
+  __shared__ uint4 ring[R::RING_SLOTS];
+  if constexpr (GROUPED)
+    if ((g.err1 && *g.err1) || (g.err2 && *g.err2)) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned w = blockIdx.x / kXcds;
+  const int y = (int)(w % (unsigned)ny);
+  const int64_t tile0 = ((int64_t)(w / (unsigned)ny) * kXcds + blockIdx.x % kXcds) * R::BM;
+  const int64_t n0 = (int64_t)y * R::BN;
+  int grp = 0;
+  if constexpr (GROUPED) {
+    static_assert(R::BM == kRelTile, "grouped tiles must match the row-range padding");
+    if (tile0 >= g.grp_ptr[g.groups]) return;
+    int hi = g.groups;  // grp_ptr[grp] <= tile0 < grp_ptr[hi]
+    while (hi - grp > 1) {
+      const int mid = (grp + hi) >> 1;
+      if (g.grp_ptr[mid] <= tile0) grp = mid;
+      else hi = mid;
+    }
+  } else if (tile0 >= g.M) {
+    return;
+  }
+  f32x4 acc[MT][NT];
+  float amax[MT];
+  auto clear = [&] {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) amax[mt] = 0.0f;
+  const float *A = static_cast<const float*>(g.a), *A2 = static_cast<const float*>(g.a2);
+  const int32_t* arow = GROUPED ? g.arow : nullptr;
+  const int64_t nch = (g.K + 31) / 32, nch2 = (g.K2 + 31) / 32;
+  const uint4* wi = static_cast<const uint4*>(g.wt) + ((int64_t)grp * ny + y) * nch * R::STAGE;
+  const bool concat = !GROUPED && g.mode == SAGA_GEMM_CONCAT;
+  for (int ph = 0; ph < (concat ? 2 : 1); ++ph)
+    R::phase(ph ? A2 : A, ph ? g.lda2 : g.lda, g.M, ph ? g.K2 : g.K,
+             ph ? static_cast<const uint4*>(g.wt2) + (int64_t)y * nch2 * R::STAGE : wi, tile0, ring,
+             amax, acc, arow);
+  bool slow = R::special(amax);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    slow |= g.wflags[((int64_t)grp * ny + y) * NT + t] != 0;
+    if (concat) slow |= g.wflags2[(int64_t)y * NT + t] != 0;
+  }
+  if (slow) {
+    clear();
+    R::native_phase(A, g.lda, g.M, g.K, static_cast<const float*>(g.w) + (int64_t)grp * g.K * g.ldw,
+                    g.ldw, g.N, n0, tile0, acc, arow);
+    if (concat)
+      R::native_phase(A2, g.lda2, g.M, g.K2, static_cast<const float*>(g.w2), g.ldw2, g.N, n0, tile0,
+                      acc);
+  }
+  const int64_t row0 = tile0 + wave * MT * 16;
+  if constexpr (GROUPED) {
+    // rows of range padding (map entry < 0) are written as zeros
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (g.arow[row0 + mt * 16 + 4 * (lane >> 4) + r] < 0) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[mt][nt][r] = 0.0f;
+        }
+  } else {
+    finish_tile(g, row0, n0, acc);
+  }
+  store_tile<float, MT, NT, R>(g, row0, n0, acc, ring);
+}
+
+// ---- float32 through Split3 ----
+// column blocks of NT 16-column tiles: as few blocks of at most eight as
+// cover N, of equal width
+struct SplitShape {
+  int nt, ny;
+  int64_t nch, img_bytes, flag_bytes;  // per K operand (and group, for the image)
+};
+SplitShape split_shape(int64_t N, int64_t K, int groups) {
+  SplitShape s;
+  const int tiles = (int)((N + 15) / 16);
+  s.ny = (tiles + 7) / 8;
+  s.nt = (tiles + s.ny - 1) / s.ny;
+  s.nch = (K + 31) / 32;
+  s.img_bytes = (int64_t)groups * s.ny * s.nt * s.nch * 3072;
+  s.flag_bytes = ((int64_t)groups * s.ny * s.nt * 4 + 255) / 256 * 256;
+  return s;
+}
+
+hipError_t pack_split(const void* w, int64_t ldw, int64_t K, int64_t N, int groups,
+                      const SplitShape& s, void* img, void* flags, hipStream_t st) {
+  hipLaunchKernelGGL(k_pack_split, dim3((unsigned)(s.ny * s.nt), (unsigned)groups),
+                     dim3(kPackThreads), 0, st, static_cast<const float*>(w), ldw, K, N, s.nt,
+                     static_cast<uint4*>(img), static_cast<int32_t*>(flags));
+  return hipGetLastError();
+}
+
+template <int MT, int NT, int NW, bool GROUPED>
+hipError_t launch_split(const GemmArgs& g, int ny, hipStream_t st) {
+  typedef Split3<MT, NT, NW> R;
+  static_assert(R::LDS_BYTES <= 160 * 1024, "LDS ring too large");
+  const int64_t mt = (g.M + R::BM - 1) / R::BM;
+  const unsigned grid = (unsigned)((mt + kXcds - 1) / kXcds * kXcds * ny);
+  hipLaunchKernelGGL((k_gemm_split<MT, NT, NW, GROUPED>), dim3(grid), dim3(R::THREADS), 0, st, g,
+                     ny);
+  return hipGetLastError();
+}
+
+// Tile shape, measured (us, float32 matrix instructions / 32 rows per wave /
+// 16 rows per wave; four waves): long K over many rows takes 32 rows a wave,
+// which halves the LDS reads per product (2^21 x 602 x 128: 2918 / 1867 / 1942;
+// 131072 x 512 x 256 in two operands: 316 / 201 / 218; 600000 x 300 x 300:
+// 1441 / 751 / 772).  Up to seven k chunks, or too few tiles to fill the chip
+// twice over, 16 rows: more waves in flight (100000 x 64 x 64: 22.0 / 21.6 /
+// 19.1; 500000 x 100 x 48: 91 / 90 / 78; 5000 x 602 x 256: 53 / 35 / 26;
+// 20000 x 512 x 80: 35 / 26 / 24).
+template <int NT, bool GROUPED>
+hipError_t dispatch_split_nt(const GemmArgs& g, const SplitShape& s, int64_t chunks, hipStream_t st) {
+  const bool tall = chunks >= 8 && (GROUPED || (g.M + 127) / 128 * s.ny >= 1024);
+  if constexpr (GROUPED)  // tiles of exactly kRelTile rows
+    return tall ? launch_split<2, NT, 4, true>(g, s.ny, st) : launch_split<1, NT, 8, true>(g, s.ny, st);
+  else
+    return tall ? launch_split<2, NT, 4, false>(g, s.ny, st) : launch_split<1, NT, 4, false>(g, s.ny, st);
+}
+
+template <bool GROUPED>
+hipError_t dispatch_split(const GemmArgs& g, const SplitShape& s, int64_t chunks, hipStream_t st) {
+  switch (s.nt) {
+    case 1: return dispatch_split_nt<1, GROUPED>(g, s, chunks, st);
+    case 2: return dispatch_split_nt<2, GROUPED>(g, s, chunks, st);
+    case 3: return dispatch_split_nt<3, GROUPED>(g, s, chunks, st);
+    case 4: return dispatch_split_nt<4, GROUPED>(g, s, chunks, st);
+    case 5: return dispatch_split_nt<5, GROUPED>(g, s, chunks, st);
+    case 6: return dispatch_split_nt<6, GROUPED>(g, s, chunks, st);
+    case 7: return dispatch_split_nt<7, GROUPED>(g, s, chunks, st);
+    default: return dispatch_split_nt<8, GROUPED>(g, s, chunks, st);
+  }
+}
+
+}  // namespace
+
+bool gemm_splits(int dtype, int mode, int64_t N, int64_t K) {
+  return dtype == SAGA_F32 && mode != SAGA_GEMM_GRU && (N > 32 || K > 256);
+}
+
+size_t split_workspace_bytes(int64_t N, int64_t K, int64_t K2, int groups) {
+  const SplitShape s = split_shape(N, K, groups), s2 = split_shape(N, K2, groups);
+  return (size_t)(s.img_bytes + s2.img_bytes + s.flag_bytes + s2.flag_bytes);
+}
+
+// Workspace: the image of w, the image of w2, then the flags of each
+hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
+  const bool grouped = g0.groups > 0, cat = !grouped && g0.mode == SAGA_GEMM_CONCAT;
+  const int groups = grouped ? g0.groups : 1;
+  const SplitShape s = split_shape(g0.N, g0.K, groups), s2 = split_shape(g0.N, cat ? g0.K2 : 0, groups);
+  if (!g0.ws || g0.ws_bytes < split_workspace_bytes(g0.N, g0.K, cat ? g0.K2 : 0, groups))
+    return hipErrorInvalidValue;
+  GemmArgs g = g0;
+  char* ws = static_cast<char*>(g.ws);
+  char* fl = ws + s.img_bytes + s2.img_bytes;
+  g.wt = ws;
+  g.wt2 = ws + s.img_bytes;
+  g.wflags = reinterpret_cast<int32_t*>(fl);
+  g.wflags2 = reinterpret_cast<int32_t*>(fl + s.flag_bytes);
+  hipError_t e = pack_split(g.w, g.ldw, g.K, g.N, groups, s, ws, fl, st);
+  if (e == hipSuccess && cat)
+    e = pack_split(g.w2, g.ldw2, g.K2, g.N, 1, s2, ws + s.img_bytes, fl + s.flag_bytes, st);
+  if (e != hipSuccess) return e;
+  const int64_t chunks = s.nch + s2.nch;
+  return grouped ? dispatch_split<true>(g, s, chunks, st) : dispatch_split<false>(g, s, chunks, st);
+}
+
+}  // namespace saga

@@ -74,10 +74,10 @@ STAGES = {
                  "bf16": [("k_gather_sum<unsigned short, 8, 1, 4, 4, false>", 1, 1, (0,)),
                           ("k_combine<unsigned short>", 1, 2, (1,))]},
                 "gather.hip"),
-    "gemm1": ({"f32": [("k_gemm<float, 2, 8,", 1, 1, (0,))],
+    "gemm1": ({"f32": [("k_gemm_split<2, 8, 4,", 1, 1, (0,))],
                "bf16": [("k_gemm_bres<2, 8, 3>", 1, 1, (0,))]},
               "gemm.hip"),
-    "gemm2": ({"f32": [("k_gemm<float, 2, 3,", 1, 1, (0,))],
+    "gemm2": ({"f32": [("k_gemm_split<1, 3, 4,", 1, 1, (0,))],
                "bf16": [("k_gemm<unsigned short, 2, 3,", 1, 1, (0,))]},
               "gemm.hip"),
 }
