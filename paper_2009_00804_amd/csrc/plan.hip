@@ -53,31 +53,10 @@ __device__ __forceinline__ int32_t block_excl_scan(int32_t v, int32_t* total) {
   return off + incl - v;
 }
 
-// ------------------------------------------------------------------------
-// functors feeding the generic scan
-// ------------------------------------------------------------------------
-struct ArrF {
-  const int32_t* p;
-  __device__ int32_t operator()(int64_t i) const { return p[i]; }
-};
 // the in-degree behind a degree-order sort key (key = 0x7fffffff - d_in)
 __device__ __forceinline__ int32_t key_degree(uint32_t key) { return (int32_t)(0x7fffffffu - key); }
-// number of segments of perm position i, from the sorted keys
-struct NsegF {
-  const uint32_t* keys;
-  int32_t T;
-  __device__ int32_t operator()(int64_t i) const {
-    const int32_t d = key_degree(keys[i]);
-    return d > T ? (d + T - 1) / T : 1;
-  }
-};
-// cost of segment s
-struct CostF {
-  const int32_t* beg;
-  const int32_t* end;
-  int32_t c;
-  __device__ int32_t operator()(int64_t i) const { return end[i] - beg[i] + c; }
-};
+// number of segments of a row of d edges
+__device__ __forceinline__ int32_t seg_count(int32_t d, int32_t T) { return d > T ? (d + T - 1) / T : 1; }
 
 // ------------------------------------------------------------------------
 // kernels
@@ -88,17 +67,15 @@ __global__ void k_zero(int32_t* p, int64_t n) {
     p[i] = 0;
 }
 
-// d_in, d_out and CSR validation; error bits go to counts[kErrFlags]
-// (edges_too: also count d_out with global atomics -- only used when the
-// source range is too large for the bucketed count below)
+// d_in, d_out (with global atomics) and CSR validation; error bits go to
+// counts[kErrFlags].  Only for graphs without the bucketed count below.
 __global__ __launch_bounds__(kThreads) void k_degrees(const int32_t* __restrict__ rp,
                                                       const int32_t* __restrict__ col, int32_t V,
-                                                      int32_t Vs, int64_t E, int edges_too,
-                                                      int32_t* d_in, int32_t* d_out,
-                                                      int32_t* counts) {
+                                                      int32_t Vs, int64_t E, int32_t* d_in,
+                                                      int32_t* d_out, int32_t* counts) {
   int err = 0;
   int maxd = 0;
-  const int64_t n = (V > E || !edges_too) ? (int64_t)V : E;
+  const int64_t n = V > E ? (int64_t)V : E;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     if (i < V) {
@@ -113,7 +90,7 @@ __global__ __launch_bounds__(kThreads) void k_degrees(const int32_t* __restrict_
         if ((int64_t)rp[V] != E) err |= 4;
       }
     }
-    if (edges_too && i < E) {
+    if (i < E) {
       int32_t c = col[i];
       if (c < 0 || c >= Vs)
         err |= 8;
@@ -141,6 +118,58 @@ __global__ __launch_bounds__(kThreads) void k_degrees(const int32_t* __restrict_
     }
     if (err) atomicOr(&counts[kErrFlags], err);
     // most workgroups already see a larger maximum: skip their atomic
+    if (maxd > __hip_atomic_load(&counts[kMaxDegree], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&counts[kMaxDegree], maxd);
+  }
+}
+
+// d_in, row_ptr validation and, per tile of kTile rows, the histogram of the
+// first radix digit (graphs whose out-degrees are counted in buckets)
+__global__ __launch_bounds__(kThreads) void k_degrees_hist(const int32_t* __restrict__ rp, int32_t V,
+                                                           int64_t E, int32_t* __restrict__ d_in,
+                                                           int32_t* __restrict__ hist, int64_t ntiles,
+                                                           int32_t* counts) {
+  __shared__ int32_t h[kBins];
+  __shared__ int s_err[kThreads / 64], s_max[kThreads / 64];
+  const int64_t tile = blockIdx.x;
+  h[threadIdx.x] = 0;
+  __syncthreads();
+  int err = 0, maxd = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int64_t i = tile * kTile + j * kThreads + threadIdx.x;
+    if (i < V) {
+      const int32_t a = rp[i], b = rp[i + 1];
+      if (b < a) err |= 2;
+      int32_t d = b - a;
+      d = d < 0 ? 0 : d;
+      d_in[i] = d;
+      maxd = d > maxd ? d : maxd;
+      if (i == 0) {
+        if (a != 0) err |= 1;
+        if ((int64_t)rp[V] != E) err |= 4;
+      }
+      atomicAdd(&h[(0x7fffffffu - (uint32_t)d) & (kBins - 1)], 1);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    err |= __shfl_xor(err, off, 64);
+    const int m = __shfl_xor(maxd, off, 64);
+    maxd = m > maxd ? m : maxd;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_err[threadIdx.x >> 6] = err;
+    s_max[threadIdx.x >> 6] = maxd;
+  }
+  __syncthreads();
+  hist[(int64_t)threadIdx.x * ntiles + tile] = h[threadIdx.x];
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < kThreads / 64; ++k) {
+      err |= s_err[k];
+      maxd = s_max[k] > maxd ? s_max[k] : maxd;
+    }
+    if (err) atomicOr(&counts[kErrFlags], err);
     if (maxd > __hip_atomic_load(&counts[kMaxDegree], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       atomicMax(&counts[kMaxDegree], maxd);
   }
@@ -193,10 +222,25 @@ constexpr int kOdCountWgs = 1024, kOdRuns = 4, kOdLoads = 4;
 static_assert(kOdBits <= 15, "the count's LDS histogram holds 2^15 counters");
 static_assert(kOdTile <= 65536, "16-bit offsets");
 static_assert(64 * kOdItems < 0xffff, "16-bit ranks within a wave");
-// workgroups per bucket in the count: about kOdCountWgs workgroups in all
-inline int outdeg_split(int64_t nb) {
+// workgroups per bucket in the count: about kOdCountWgs workgroups in all, at
+// most 16 a bucket (each leaves a partial histogram to add up), or with few
+// buckets up to 64 where each still has 2^16 entries (16,000 sources, 2.4e7
+// edges: whole plan 738 -> 345 us; with 19 buckets, 6e6 edges: 131 -> 165)
+inline int outdeg_split(int64_t nb, int64_t E) {
   const int64_t s = nb >= kOdCountWgs || nb < 1 ? 1 : kOdCountWgs / nb;
-  return (int)(s > 16 ? 16 : s);
+  const int64_t most = nb > 8 || E >> 16 < 16 ? 16 : E >> 16 > 64 ? 64 : E >> 16;
+  return (int)(s > most ? most : s);
+}
+// Few buckets and few edges: no tile sort; every bucket's workgroups read all
+// of col_idx and count their own ids.  The re-reads come from L2; the tile
+// sort costs two launches and gives a bucket's few workgroups long runs.
+// Measured (us, tile sort / direct): the count alone, 100,000 sources, 1.3e6
+// edges 80 / 21; 15,000 sources, 1.65e5 edges 94 / 9; the whole plan, 100,000
+// sources, 1e7 edges 127 / 87; 40,000 sources, 2.4e7 edges 279 / 111; 262,144
+// sources, 1.3e6 edges 173 / 59; but 300,000 sources, 6e6 edges 131 / 164 and
+// 10^6 sources, 2e6 edges 105 / 145.
+inline bool outdeg_direct(int64_t nb, int64_t E) {
+  return nb * E <= (nb <= 8 ? int64_t(256) << 20 : int64_t(32) << 20);
 }
 inline size_t outdeg_bin_lds(int nb) {
   return (size_t)kOdWaves * nb * 4 + (size_t)kOdTile * 2;
@@ -302,7 +346,7 @@ __global__ __launch_bounds__(kOdThreads) void k_outdeg_bin(const int32_t* __rest
 }
 
 // Bucket b's entries, from the runs of tiles [t0, t1) (slice s of
-// outdeg_split(nb)), counted into LDS; the histogram goes to
+// outdeg_split), counted into LDS; the histogram goes to
 // part[s][b * kOdBucket + i].  Each wave takes R tiles at a time and reads
 // the first J * 64 entries of each run before counting, so that R * J loads
 // are in flight; longer runs finish in a loop.
@@ -369,6 +413,37 @@ __global__ __launch_bounds__(1024) void k_outdeg_count(const uint16_t* __restric
   for (int i = threadIdx.x; i < kOdBucket; i += 1024) pw[i] = h[i];
 }
 
+// The direct count: workgroup (b, s) counts the ids of bucket b among slice s
+// of col_idx; the workgroups of bucket 0 also check every id.
+__global__ __launch_bounds__(1024) void k_outdeg_direct(const int32_t* __restrict__ col, int64_t E,
+                                                        int32_t Vs, int nb, int32_t* __restrict__ part,
+                                                        int32_t* counts) {
+  __shared__ int32_t h[kOdBucket];
+  const int b = blockIdx.x, s = blockIdx.y, S = gridDim.y;
+  for (int i = threadIdx.x; i < kOdBucket; i += 1024) h[i] = 0;
+  __syncthreads();
+  const int64_t e0 = E * s / S, e1 = E * (s + 1) / S;
+  constexpr int J = 8;  // loads in flight per thread
+  bool bad = false;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += 1024 * J) {
+    int32_t c[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) c[j] = e + j * 1024 < e1 ? col[e + j * 1024] : -2;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (c[j] >= 0 && c[j] < Vs) {
+        if (c[j] >> kOdBits == b) atomicAdd(&h[c[j] & (kOdBucket - 1)], 1);
+      } else {
+        bad |= e + j * 1024 < e1;
+      }
+    }
+  }
+  if (b == 0 && __any(bad) && (threadIdx.x & 63) == 0) atomicOr(&counts[kErrFlags], 8);
+  __syncthreads();
+  int32_t* pw = part + (int64_t)s * nb * kOdBucket + (int64_t)b * kOdBucket;
+  for (int i = threadIdx.x; i < kOdBucket; i += 1024) pw[i] = h[i];
+}
+
 // d_out[v] = the sum of the S partial counts, four sources per thread as
 // 16-byte loads (part and d_out are 256-byte aligned, stride a multiple of 4)
 __global__ __launch_bounds__(kThreads) void k_outdeg_reduce(const int32_t* __restrict__ part,
@@ -381,6 +456,7 @@ __global__ __launch_bounds__(kThreads) void k_outdeg_reduce(const int32_t* __res
   const int64_t g0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, gs = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = g0; i < n4; i += gs) {
     int4 sum = make_int4(0, 0, 0, 0);
+#pragma unroll 8
     for (int w = 0; w < S; ++w) {
       const int4 x = reinterpret_cast<const int4*>(part + w * stride)[i];
       sum.x += x.x;
@@ -397,6 +473,19 @@ __global__ __launch_bounds__(kThreads) void k_outdeg_reduce(const int32_t* __res
   }
 }
 
+// A pass over digit `shift` moves nothing when no in-degree reaches it: the
+// digits of 0x7fffffff - d are then all the same.  Such passes are skipped on
+// the device (the first never is), so the order ends in the buffers of the
+// last pass that ran.
+__device__ __forceinline__ bool radix_skips(const int32_t* counts, int shift) {
+  return shift > 0 && (counts[kMaxDegree] >> shift) == 0;
+}
+// passes that ran
+__device__ __forceinline__ int radix_passes(const int32_t* counts) {
+  const int m = counts[kMaxDegree];
+  return m >> 8 == 0 ? 1 : m >> 16 == 0 ? 2 : m >> 24 == 0 ? 3 : 4;
+}
+
 // per-tile digit histogram, stored digit-major: hist[digit * ntiles + tile]
 template <bool FIRST>
 __global__ __launch_bounds__(kThreads) void k_radix_hist(const int32_t* __restrict__ d_in,
@@ -404,7 +493,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const int32_t* __restri
                                                          int32_t n, int shift,
                                                          int32_t* __restrict__ hist, int64_t ntiles,
                                                          const int32_t* counts) {
-  if (counts[kErrFlags]) return;
+  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
   __shared__ int32_t h[kBins];
   const int64_t tile = xcd_tile(ntiles);
   if (tile < 0) return;
@@ -422,42 +511,67 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const int32_t* __restri
   hist[(int64_t)threadIdx.x * ntiles + tile] = h[threadIdx.x];
 }
 
-// Stable scatter.  Items are visited in index order (round j, thread t ->
-// item j*256 + t); an item's rank among equal digits inside the tile comes
-// from a wave-level match (8 ballots) plus the counts of lower waves and of
-// earlier rounds, so equal keys keep their input order.
+// Stable scatter.  Wave w of a tile takes its w-th quarter, 64 items at a time
+// in index order: an item's rank among the wave's equal digits is the wave's
+// count so far plus a match within the 64 (8 ballots).  The waves' counts are
+// then added up in wave order, so equal keys keep their input order, with
+// three workgroup barriers a tile (a barrier per 256 items: 13.5 against 11.3
+// us for 49 tiles).
 // Each item carries a second value, its row's first CSR entry (row_ptr[v]
 // on the first pass), so that the segment builder reads it in perm order
 // instead of gathering row_ptr at random.
-template <bool FIRST>
+// INSCAN: `offsets` holds the plain histograms, and each workgroup derives its
+// own digit offsets from them (at most kInscanTiles tiles: one thread reads
+// its digit's row), instead of from a scan in launches of its own.
+constexpr int64_t kInscanTiles = 128;
+template <bool FIRST, bool INSCAN>
 __global__ __launch_bounds__(kThreads) void k_radix_scatter(
     const int32_t* __restrict__ d_in, const uint32_t* __restrict__ keys_in,
     const int32_t* __restrict__ vals_in, const int32_t* __restrict__ rb_in, int32_t n, int shift,
     const int32_t* __restrict__ offsets, int64_t ntiles, uint32_t* __restrict__ keys_out,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ rb_out, const int32_t* counts) {
-  if (counts[kErrFlags]) return;
-  __shared__ int32_t running[kBins];
-  __shared__ int32_t wcnt[kThreads / 64][kBins];
-  const int t = threadIdx.x, w = t >> 6;
+  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
+  constexpr int NW = kThreads / 64;
+  __shared__ int32_t wcnt[NW][kBins];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   const int64_t tile = xcd_tile(ntiles);
   if (tile < 0) return;
-  running[t] = offsets[(int64_t)t * ntiles + tile];
 #pragma unroll
-  for (int k = 0; k < kThreads / 64; ++k) wcnt[k][t] = 0;
-  __syncthreads();
-  const uint64_t lt = lanemask_lt();
+  for (int k = 0; k < NW; ++k) wcnt[k][t] = 0;
+  uint32_t key[kItems];
+  int32_t val[kItems], rb[kItems], rank[kItems];
+#pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    const int64_t i = tile * kTile + j * kThreads + t;
-    const bool valid = i < n;
-    uint32_t key = 0;
-    int32_t val = 0, rb = 0;
-    int dg = 0;
-    if (valid) {
-      key = FIRST ? (0x7fffffffu - (uint32_t)d_in[i]) : keys_in[i];
-      val = FIRST ? (int32_t)i : vals_in[i];
-      rb = rb_in[i];
-      dg = (key >> shift) & (kBins - 1);
+    const int64_t i = tile * kTile + (w * kItems + j) * 64 + lane;
+    if (i < n) {
+      key[j] = FIRST ? (0x7fffffffu - (uint32_t)d_in[i]) : keys_in[i];
+      val[j] = FIRST ? (int32_t)i : vals_in[i];
+      rb[j] = rb_in[i];
     }
+  }
+  int32_t start;  // of digit t in the output, then of this tile's items of it
+  if constexpr (INSCAN) {
+    int32_t before = 0, all = 0;
+    const int32_t* row = offsets + (int64_t)t * ntiles;
+#pragma unroll 8
+    for (int64_t k = 0; k < ntiles; ++k) {
+      const int32_t x = row[k];
+      before += k < tile ? x : 0;
+      all += x;
+    }
+    int32_t tot;
+    start = block_excl_scan<kThreads>(all, &tot) + before;
+  } else {
+    start = offsets[(int64_t)t * ntiles + tile];
+    __syncthreads();
+  }
+  const uint64_t lt = lanemask_lt();
+  int32_t* cnt = wcnt[w];
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int64_t i = tile * kTile + (w * kItems + j) * 64 + lane;
+    const bool valid = i < n;
+    const int dg = valid ? (key[j] >> shift) & (kBins - 1) : 0;
     uint64_t m = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -465,53 +579,57 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
       uint64_t bal = __ballot(valid && bit);
       m &= bit ? bal : ~bal;
     }
-    const int rank = __popcll(m & lt);
-    if (valid && rank == 0) wcnt[w][dg] = __popcll(m);
-    __syncthreads();
-    if (valid) {
-      int32_t pos = running[dg] + rank;
-      for (int k = 0; k < w; ++k) pos += wcnt[k][dg];
+    const int r = __popcll(m & lt);
+    const int32_t have = valid ? cnt[dg] : 0;
+    rank[j] = have + r;
+    // the wave's LDS accesses complete in program order: every lane has read
+    // the count before its group's first lane moves it on
+    asm volatile("" ::: "memory");
+    if (valid && r == 0) cnt[dg] = have + __popcll(m);
+    asm volatile("" ::: "memory");
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {  // thread t: digit t
+    const int32_t x = wcnt[k][t];
+    wcnt[k][t] = start;
+    start += x;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int64_t i = tile * kTile + (w * kItems + j) * 64 + lane;
+    if (i < n) {
+      const int32_t pos = cnt[(key[j] >> shift) & (kBins - 1)] + rank[j];
       if (pos >= 0 && pos < n) {
-        keys_out[pos] = key;
-        vals_out[pos] = val;
-        rb_out[pos] = rb;
+        keys_out[pos] = key[j];
+        vals_out[pos] = val[j];
+        rb_out[pos] = rb[j];
       } else {
         atomicOr(const_cast<int32_t*>(counts) + kErrFlags, kErrInternal);
       }
     }
-    __syncthreads();
-    int32_t tot = 0;
-#pragma unroll
-    for (int k = 0; k < kThreads / 64; ++k) {
-      tot += wcnt[k][t];
-      wcnt[k][t] = 0;
-    }
-    running[t] += tot;
-    __syncthreads();
   }
 }
 
-template <class F>
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(F f, int64_t n_host,
-                                                          const int32_t* n_dev,
-                                                          int32_t* tile_sums,
+__global__ __launch_bounds__(kThreads) void k_scan_reduce(const int32_t* __restrict__ in, int64_t n,
+                                                          int32_t* tile_sums, int shift,
                                                           const int32_t* counts) {
-  if (counts[kErrFlags]) return;
-  const int64_t n = n_dev ? ((int64_t)*n_dev < n_host ? (int64_t)*n_dev : n_host) : n_host;
+  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
   const int64_t base = blockIdx.x * (int64_t)kTile + threadIdx.x * kItems;
   int32_t s = 0;
 #pragma unroll
   for (int k = 0; k < kItems; ++k)
-    if (base + k < n) s += f(base + k);
+    if (base + k < n) s += in[base + k];
   int32_t tot;
   block_excl_scan<kThreads>(s, &tot);
   if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
 }
 
 // exclusive scan of the tile sums by one workgroup of 1024 threads
-__global__ __launch_bounds__(1024) void k_scan_tilesums(int32_t* ts, int64_t nt, int32_t* total,
+__global__ __launch_bounds__(1024) void k_scan_tilesums(int32_t* ts, int64_t nt, int shift,
                                                         const int32_t* counts) {
-  if (counts[kErrFlags]) return;
+  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
   __shared__ int32_t carry_s;
   if (threadIdx.x == 0) carry_s = 0;
   __syncthreads();
@@ -526,22 +644,19 @@ __global__ __launch_bounds__(1024) void k_scan_tilesums(int32_t* ts, int64_t nt,
     if (threadIdx.x == 0) carry_s = carry + tot;
     __syncthreads();
   }
-  if (threadIdx.x == 0 && total) *total = carry_s;
 }
 
-template <class F>
-__global__ __launch_bounds__(kThreads) void k_scan_apply(F f, int64_t n_host,
-                                                         const int32_t* n_dev,
+__global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t* in, int64_t n,
                                                          const int32_t* tile_sums,
-                                                         int32_t* out, const int32_t* counts) {
-  if (counts[kErrFlags]) return;
-  const int64_t n = n_dev ? ((int64_t)*n_dev < n_host ? (int64_t)*n_dev : n_host) : n_host;
+                                                         int32_t* out, int shift,
+                                                         const int32_t* counts) {
+  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
   const int64_t base = blockIdx.x * (int64_t)kTile + threadIdx.x * kItems;
   int32_t v[kItems];
   int32_t s = 0;
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    v[k] = base + k < n ? f(base + k) : 0;
+    v[k] = base + k < n ? in[base + k] : 0;
     s += v[k];
   }
   int32_t tot;
@@ -553,82 +668,159 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(F f, int64_t n_host,
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_segments(const uint32_t* __restrict__ keys,
-                                                       const int32_t* __restrict__ rbeg,
-                                                       const int32_t* __restrict__ perm,
-                                                       const int32_t* __restrict__ first,
-                                                       int32_t V, int32_t T, int64_t max_seg,
-                                                       int32_t* seg_row, int32_t* seg_beg,
-                                                       int32_t* seg_end, int32_t* counts) {
+// ------------------------------------------------------------------------
+// Segments and row blocks, from the degree order.  Position i of the order has
+// ns(i) segments of total cost d_i + ns(i) row_cost, so one prefix sum over
+// the rows gives both the first segment of every row and the cost before it;
+// the segments inside a row follow from those.  k_seg_sums: each tile's totals
+// (y: the tile sums of segments and of cost).  k_seg_emit: a workgroup adds up
+// the tiles before its own (or reads them scanned), scans its rows in LDS and
+// writes its segments slot by slot, so that a hub row's hundreds of segments
+// are spread over the workgroup.  The first tile, the hubs', takes longest; 512
+// rows and a shift for the default power-of-two block cost keep it short.
+// ------------------------------------------------------------------------
+struct Order {  // the degree order's buffers: pass p ends in keys[p % 2] ..
+  const uint32_t* keys[2];
+  const int32_t* vals[2];
+  const int32_t* rbeg[2];
+};
+constexpr int kSegTile = 512;        // rows per workgroup, one per thread
+constexpr int64_t kSumTiles = 4096;  // more tiles: their sums are scanned by a launch of its own
+
+__global__ __launch_bounds__(kSegTile) void k_seg_sums(Order o, int32_t V, int32_t T, int32_t c,
+                                                       int32_t* __restrict__ sums, int64_t ntiles,
+                                                       const int32_t* counts) {
   if (counts[kErrFlags]) return;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < V;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t v = perm[i];
-    if (v < 0 || v >= V) {
-      atomicOr(&counts[kErrFlags], kErrInternal);
-      return;
-    }
+  const uint32_t* __restrict__ keys = o.keys[(radix_passes(counts) - 1) & 1];
+  int32_t ns = 0, cost = 0;
+  const int64_t i = blockIdx.x * (int64_t)kSegTile + threadIdx.x;
+  if (i < V) {
     const int32_t d = key_degree(keys[i]);
-    const int32_t f = first[i];
-    const int32_t ns = d > T ? (d + T - 1) / T : 1;
-    if (f < 0 || (int64_t)f + ns > max_seg) {
-      atomicOr(&counts[kErrFlags], kErrInternal);
-      return;
-    }
-    const int32_t b0 = rbeg[i], e0 = b0 + d;
-    for (int32_t j = 0; j < ns; ++j) {
-      const int32_t b = b0 + j * T;
-      seg_row[f + j] = v;
-      seg_beg[f + j] = b;
-      seg_end[f + j] = (e0 - b) > T ? b + T : e0;
-    }
-    const bool split = d > T;
-    const bool next_split = (i + 1 < V) && key_degree(keys[i + 1]) > T;
-    if (split && !next_split) {
-      counts[kNSplit] = (int32_t)(i + 1);
-      counts[kSSplit] = f + ns;
-    }
-    if (i == V - 1) counts[kNumSegments] = f + ns;
+    ns = seg_count(d, T);
+    cost = d + ns * c;
+  }
+  int32_t tn, tc;
+  block_excl_scan<kSegTile>(ns, &tn);
+  block_excl_scan<kSegTile>(cost, &tc);
+  if (threadIdx.x == 0) {
+    sums[blockIdx.x] = tn;
+    sums[ntiles + blockIdx.x] = tc;
   }
 }
 
-// block b holds the segments s with floor(P(s) / B) == b; consecutive
-// segments differ in P by at most seg_len + row_cost <= B, so no block id
-// is skipped.
-__global__ __launch_bounds__(kThreads) void k_blocks(const int32_t* __restrict__ P, int32_t B,
-                                                     int64_t max_seg, int64_t max_blocks,
-                                                     int32_t* block_ptr, int32_t* counts) {
+__global__ __launch_bounds__(kSegTile) void k_seg_emit(Order o, int32_t V, int32_t T, int32_t c, int32_t B,
+                                                       int bshift,
+                                                       const int32_t* __restrict__ sums, int64_t ntiles,
+                                                       int scanned, int64_t max_seg, int64_t max_blocks,
+                                                       int32_t* __restrict__ perm,
+                                                       int32_t* __restrict__ first,
+                                                       int32_t* __restrict__ seg_row,
+                                                       int32_t* __restrict__ seg_beg,
+                                                       int32_t* __restrict__ seg_end,
+                                                       int32_t* __restrict__ block_ptr, int32_t* counts) {
   if (counts[kErrFlags]) return;
-  const int32_t S = counts[kNumSegments];
-  if (S > max_seg) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&counts[kErrFlags], kErrInternal);
+  __shared__ int32_t s_deg[kSegTile], s_row[kSegTile], s_rb[kSegTile], s_first[kSegTile + 1], s_cost[kSegTile];
+  const int64_t tile = blockIdx.x;
+  const int t = threadIdx.x;
+  const int last_pass = (radix_passes(counts) - 1) & 1;
+  const uint32_t* __restrict__ keys = o.keys[last_pass];
+  const int32_t* __restrict__ vals = o.vals[last_pass];
+  const int32_t* __restrict__ rbeg = o.rbeg[last_pass];
+  int32_t base_n, base_c;  // segments and cost before this tile
+  if (scanned) {
+    base_n = sums[tile];
+    base_c = sums[ntiles + tile];
+  } else {
+    int32_t a = 0, b = 0;
+    for (int64_t k = t; k < tile; k += kSegTile) {
+      a += sums[k];
+      b += sums[ntiles + k];
+    }
+    block_excl_scan<kSegTile>(a, &base_n);
+    block_excl_scan<kSegTile>(b, &base_c);
+  }
+  const int64_t i0 = tile * kSegTile;
+  const int n = V - i0 < kSegTile ? (int)(V - i0) : kSegTile;
+  bool bad = false;
+  int32_t ns = 0, cost = 0;
+  if (t < n) {
+    const int32_t v = vals[i0 + t], d = key_degree(keys[i0 + t]);
+    bad = v < 0 || v >= V;
+    s_deg[t] = d;
+    s_row[t] = v;
+    s_rb[t] = rbeg[i0 + t];
+    perm[i0 + t] = v;
+    ns = seg_count(d, T);
+    cost = d + ns * c;
+  }
+  int32_t tile_n, tile_c;
+  s_first[t] = block_excl_scan<kSegTile>(ns, &tile_n);
+  s_cost[t] = block_excl_scan<kSegTile>(cost, &tile_c) + base_c;
+  if (t == 0 && n == kSegTile) s_first[n] = tile_n;  // (a short tile's scan holds it)
+  bad |= base_n < 0 || tile_n < n || (int64_t)base_n + tile_n > max_seg;
+  if (__syncthreads_or(bad)) {
+    if (t == 0) atomicOr(&counts[kErrFlags], kErrInternal);
     return;
   }
-  for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < S;
-       s += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t b = P[s] / B;
-    if (b < 0 || b >= max_blocks) {
-      atomicOr(&counts[kErrFlags], kErrInternal);
-      return;
+  const bool last_tile = i0 + n == V;
+  if (const int r = t; r < n) {
+    first[i0 + r] = base_n + s_first[r];
+    // the last split row: the next one fits a segment
+    if (s_deg[r] > T) {
+      const int32_t next = r + 1 < n ? s_deg[r + 1] : last_tile ? 0 : key_degree(keys[i0 + n]);
+      if (next <= T) {
+        counts[kNSplit] = (int32_t)(i0 + r + 1);
+        counts[kSSplit] = base_n + s_first[r + 1];
+      }
     }
-    if (s == 0 || P[s - 1] / B != b) block_ptr[b] = (int32_t)s;
-    if (s == S - 1) {
-      block_ptr[b + 1] = S;
-      counts[kNumBlocks] = b + 1;
+  }
+  if (last_tile && t == 0) {
+    first[V] = base_n + tile_n;
+    counts[kNumSegments] = base_n + tile_n;
+  }
+  // block b holds the segments s with floor(P(s) / B) == b; consecutive
+  // segments differ in P by at most seg_len + row_cost <= B, so no block id
+  // is skipped
+  auto block_of = [&](int32_t P) { return bshift >= 0 ? P >> bshift : P / B; };
+  for (int q = t; q < tile_n; q += kSegTile) {
+    int r = q;
+    if (tile_n != n) {  // rows of several segments: the row whose range holds q
+      r = 0;
+#pragma unroll
+      for (int step = kSegTile / 2; step > 0; step >>= 1)
+        if (r + step < n && s_first[r + step] <= q) r += step;
+    }
+    const int32_t j = q - s_first[r], d = s_deg[r], s = base_n + q;
+    const int32_t b = s_rb[r] + j * T, left = d - j * T;
+    seg_row[s] = s_row[r];
+    seg_beg[s] = b;
+    seg_end[s] = b + (left > T ? T : left);
+    const int32_t P = s_cost[r] + j * (T + c), blk = block_of(P);
+    int32_t prev = T + c;  // cost of segment s - 1
+    if (j == 0 && s > 0) {
+      const int32_t dp = r > 0 ? s_deg[r - 1] : key_degree(keys[i0 - 1]);
+      prev = dp - (seg_count(dp, T) - 1) * T + c;
+    }
+    if (blk < 0 || blk >= max_blocks) {
+      atomicOr(&counts[kErrFlags], kErrInternal);
+    } else {
+      if (s == 0 || block_of(P - prev) != blk) block_ptr[blk] = s;
+      if (last_tile && q == tile_n - 1) {
+        block_ptr[blk + 1] = s + 1;
+        counts[kNumBlocks] = blk + 1;
+      }
     }
   }
 }
 
-template <class F>
-void scan(F f, int64_t n_host, const int32_t* n_dev, int32_t* out, int32_t* total,
-          int32_t* tile_sums, const int32_t* counts, hipStream_t st) {
-  const int64_t nt = cdiv(n_host, kTile);
+// exclusive scan of n ints, in launches of its own (skipped with the pass)
+void scan(const int32_t* in, int64_t n, int32_t* out, int32_t* tile_sums, int shift, const int32_t* counts,
+          hipStream_t st) {
+  const int64_t nt = cdiv(n, kTile);
   if (nt == 0) return;
-  hipLaunchKernelGGL(k_scan_reduce<F>, dim3(nt), dim3(kThreads), 0, st, f, n_host, n_dev,
-                     tile_sums, counts);
-  hipLaunchKernelGGL(k_scan_tilesums, dim3(1), dim3(1024), 0, st, tile_sums, nt, total, counts);
-  hipLaunchKernelGGL(k_scan_apply<F>, dim3(nt), dim3(kThreads), 0, st, f, n_host, n_dev,
-                     tile_sums, out, counts);
+  hipLaunchKernelGGL(k_scan_reduce, dim3(nt), dim3(kThreads), 0, st, in, n, tile_sums, shift, counts);
+  hipLaunchKernelGGL(k_scan_tilesums, dim3(1), dim3(1024), 0, st, tile_sums, nt, shift, counts);
+  hipLaunchKernelGGL(k_scan_apply, dim3(nt), dim3(kThreads), 0, st, in, n, tile_sums, out, shift, counts);
 }
 
 inline unsigned grid_for(int64_t n, int64_t cap = 16384) {
@@ -650,15 +842,13 @@ bool plan_layout(int32_t V, int32_t Vs, int64_t E, int32_t T, int32_t B, int32_t
   L->max_split = E / (int64_t(T) + 1) < V ? E / (int64_t(T) + 1) : V;
   L->max_split_segments = cdiv(E, T) + L->max_split;
   L->radix_tiles = cdiv(V, kTile);
-  L->scan_tiles_rows = cdiv(V, kTile);
-  L->scan_tiles_segs = cdiv(L->max_segments, kTile);
+  L->scan_tiles_rows = cdiv(V, kSegTile);
   const int64_t hist_n = (int64_t)kBins * L->radix_tiles;
   L->outdeg_nb = cdiv(Vs, kOdBucket);
   L->edge_tiles = cdiv(E, kOdTile);
   L->outdeg_bucketed = L->outdeg_nb > 0 && L->outdeg_nb <= kOdMaxBuckets && E > 0;
   int64_t scan_tiles = cdiv(hist_n, kTile);
-  if (L->scan_tiles_rows > scan_tiles) scan_tiles = L->scan_tiles_rows;
-  if (L->scan_tiles_segs > scan_tiles) scan_tiles = L->scan_tiles_segs;
+  if (2 * L->scan_tiles_rows > scan_tiles) scan_tiles = 2 * L->scan_tiles_rows;
 
   size_t o = 0;
   auto take = [&](int64_t n_int) {
@@ -677,16 +867,14 @@ bool plan_layout(int32_t V, int32_t Vs, int64_t E, int32_t T, int32_t B, int32_t
   L->off_counts = take(kCountSlots);
   L->off_scratch = o;
   // scratch: keysA, valsA, keysB, valsB, row begins A and B, hist, tile
-  // sums, cost prefix, bucketed source ids, bucket run starts, partial
-  // out-degree histograms
-  const bool bk = L->outdeg_bucketed;
+  // sums, bucketed source ids, bucket run starts, partial out-degree histograms
+  const bool bk = L->outdeg_bucketed, sorted = bk && !outdeg_direct(L->outdeg_nb, E);
   take(V); take(V); take(V); take(V); take(V); take(V);
   take(hist_n);
   take(scan_tiles + 1);
-  take(L->max_segments);
-  take(bk ? cdiv(E, 2) : 0);
-  take(bk ? (L->outdeg_nb + 1) * L->edge_tiles : 0);
-  take(bk ? (int64_t)outdeg_split(L->outdeg_nb) * L->outdeg_nb * kOdBucket : 0);
+  take(sorted ? cdiv(E, 2) : 0);
+  take(sorted ? (L->outdeg_nb + 1) * L->edge_tiles : 0);
+  take(bk ? (int64_t)outdeg_split(L->outdeg_nb, E) * L->outdeg_nb * kOdBucket : 0);
   L->scratch_bytes = o - L->off_scratch;
   L->total = o;
   return true;
@@ -712,15 +900,13 @@ hipError_t launch_plan_build(const saga_plan& p, const PlanLayout& L, hipStream_
   const int64_t ntiles = L.radix_tiles;
   int32_t* hist = reinterpret_cast<int32_t*>(take((int64_t)kBins * ntiles));
   int64_t scan_tiles = cdiv((int64_t)kBins * ntiles, kTile);
-  if (L.scan_tiles_rows > scan_tiles) scan_tiles = L.scan_tiles_rows;
-  if (L.scan_tiles_segs > scan_tiles) scan_tiles = L.scan_tiles_segs;
+  if (2 * L.scan_tiles_rows > scan_tiles) scan_tiles = 2 * L.scan_tiles_rows;
   int32_t* tile_sums = reinterpret_cast<int32_t*>(take(scan_tiles + 1));
-  int32_t* P = reinterpret_cast<int32_t*>(take(L.max_segments));
-  const bool bk = L.outdeg_bucketed;
-  uint16_t* bucketed = reinterpret_cast<uint16_t*>(take(bk ? cdiv(E, 2) : 0));
-  int32_t* oloc = reinterpret_cast<int32_t*>(take(bk ? (L.outdeg_nb + 1) * L.edge_tiles : 0));
+  const bool bk = L.outdeg_bucketed, sorted = bk && !outdeg_direct(L.outdeg_nb, E);
+  uint16_t* bucketed = reinterpret_cast<uint16_t*>(take(sorted ? cdiv(E, 2) : 0));
+  int32_t* oloc = reinterpret_cast<int32_t*>(take(sorted ? (L.outdeg_nb + 1) * L.edge_tiles : 0));
   int32_t* opart = reinterpret_cast<int32_t*>(
-      take(bk ? (int64_t)outdeg_split(L.outdeg_nb) * L.outdeg_nb * kOdBucket : 0));
+      take(bk ? (int64_t)outdeg_split(L.outdeg_nb, E) * L.outdeg_nb * kOdBucket : 0));
 
   hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, p.counts, (int64_t)kCountSlots);
   if (Vs > 0 && !L.outdeg_bucketed)
@@ -747,59 +933,74 @@ hipError_t launch_plan_build(const saga_plan& p, const PlanLayout& L, hipStream_
     }
     return hipGetLastError();
   }
-  const int edges_too = L.outdeg_bucketed ? 0 : 1;
-  hipLaunchKernelGGL(k_degrees, dim3(grid_for(edges_too && E > V ? E : V, 2048)), dim3(kThreads), 0, qst,
-                     p.row_ptr, p.col_idx, V, Vs, E, edges_too, p.d_in, p.d_out, p.counts);
   if (L.outdeg_bucketed) {
+    hipLaunchKernelGGL(k_degrees_hist, dim3(ntiles), dim3(kThreads), 0, qst, p.row_ptr, V, E, p.d_in,
+                       hist, ntiles, p.counts);
     const int nb = (int)L.outdeg_nb;
     const int64_t et = L.edge_tiles;
-    const int S = outdeg_split(nb);
-    hipLaunchKernelGGL(k_outdeg_bin, dim3(xcd_grid(et)), dim3(kOdThreads), outdeg_bin_lds(nb), st,
-                       p.col_idx, E, Vs, nb, et, bucketed, oloc, p.counts);
-    hipLaunchKernelGGL(k_outdeg_count, dim3(xcd_grid(nb), S), dim3(1024), 0, st, bucketed, oloc, et,
-                       nb, E, opart, p.counts);
+    const int S = outdeg_split(nb, E);
+    if (sorted) {
+      hipLaunchKernelGGL(k_outdeg_bin, dim3(xcd_grid(et)), dim3(kOdThreads), outdeg_bin_lds(nb), st,
+                         p.col_idx, E, Vs, nb, et, bucketed, oloc, p.counts);
+      hipLaunchKernelGGL(k_outdeg_count, dim3(xcd_grid(nb), S), dim3(1024), 0, st, bucketed, oloc, et,
+                         nb, E, opart, p.counts);
+    } else {
+      hipLaunchKernelGGL(k_outdeg_direct, dim3(nb, S), dim3(1024), 0, st, p.col_idx, E, Vs, nb, opart,
+                         p.counts);
+    }
     hipLaunchKernelGGL(k_outdeg_reduce, dim3(grid_for((Vs + 3) / 4)), dim3(kThreads), 0, st, opart, nb,
                        S, Vs, p.d_out, p.counts);
+  } else {
+    hipLaunchKernelGGL(k_degrees, dim3(grid_for(E > V ? E : V, 2048)), dim3(kThreads), 0, qst, p.row_ptr,
+                       p.col_idx, V, Vs, E, p.d_in, p.d_out, p.counts);
+    hipLaunchKernelGGL(k_radix_hist<true>, dim3(xcd_grid(ntiles)), dim3(kThreads), 0, qst, p.d_in,
+                       static_cast<const uint32_t*>(nullptr), V, 0, hist, ntiles, p.counts);
   }
   st = qst;  // the row order
 
-  // degree order: 4 stable passes of 8 bits over key = 0x7fffffff - d_in;
-  // the sorted keys end in keysB, the row begins in rbB
+  // degree order: stable passes of 8 bits over key = 0x7fffffff - d_in, as
+  // many as an in-degree of at most E has digits
   const uint32_t* kin[4] = {nullptr, keysA, keysB, keysA};
   const int32_t* vin[4] = {nullptr, valsA, valsB, valsA};
   const int32_t* rin[4] = {p.row_ptr, rbA, rbB, rbA};
   uint32_t* kout[4] = {keysA, keysB, keysA, keysB};
-  int32_t* vout[4] = {valsA, valsB, valsA, p.perm};
+  int32_t* vout[4] = {valsA, valsB, valsA, valsB};
   int32_t* rout[4] = {rbA, rbB, rbA, rbB};
-  for (int pass = 0; pass < 4; ++pass) {
+  const bool inscan = ntiles <= kInscanTiles;
+  const dim3 rg(xcd_grid(ntiles)), rb(kThreads);
+  for (int pass = 0; pass < 4 && (pass == 0 || E >> (8 * pass) > 0); ++pass) {
     const int shift = 8 * pass;
-    if (pass == 0)
-      hipLaunchKernelGGL(k_radix_hist<true>, dim3(xcd_grid(ntiles)), dim3(kThreads), 0, st, p.d_in,
-                         kin[pass], V, shift, hist, ntiles, p.counts);
-    else
-      hipLaunchKernelGGL(k_radix_hist<false>, dim3(xcd_grid(ntiles)), dim3(kThreads), 0, st, p.d_in,
-                         kin[pass], V, shift, hist, ntiles, p.counts);
-    scan(ArrF{hist}, (int64_t)kBins * ntiles, nullptr, hist, nullptr, tile_sums, p.counts, st);
-    if (pass == 0)
-      hipLaunchKernelGGL((k_radix_scatter<true>), dim3(xcd_grid(ntiles)), dim3(kThreads), 0, st,
-                         p.d_in, kin[pass], vin[pass], rin[pass], V, shift, hist, ntiles,
-                         kout[pass], vout[pass], rout[pass], p.counts);
-    else
-      hipLaunchKernelGGL((k_radix_scatter<false>), dim3(xcd_grid(ntiles)), dim3(kThreads), 0, st,
-                         p.d_in, kin[pass], vin[pass], rin[pass], V, shift, hist, ntiles,
-                         kout[pass], vout[pass], rout[pass], p.counts);
+    if (pass > 0)
+      hipLaunchKernelGGL(k_radix_hist<false>, rg, rb, 0, st, p.d_in, kin[pass], V, shift, hist, ntiles,
+                         p.counts);
+    if (!inscan) scan(hist, (int64_t)kBins * ntiles, hist, tile_sums, shift, p.counts, st);
+#define SAGA_SCATTER(FIRST, IN)                                                                    \
+  hipLaunchKernelGGL((k_radix_scatter<FIRST, IN>), rg, rb, 0, st, p.d_in, kin[pass], vin[pass],     \
+                     rin[pass], V, shift, hist, ntiles, kout[pass], vout[pass], rout[pass], p.counts)
+    if (pass == 0 && inscan) SAGA_SCATTER(true, true);
+    else if (pass == 0) SAGA_SCATTER(true, false);
+    else if (inscan) SAGA_SCATTER(false, true);
+    else SAGA_SCATTER(false, false);
+#undef SAGA_SCATTER
   }
 
-  // segments per row in perm order -> row_seg_first (total at [V])
-  scan(NsegF{keysB, T}, V, nullptr, p.row_seg_first, p.row_seg_first + V, tile_sums, p.counts, st);
-  hipLaunchKernelGGL(k_segments, dim3(grid_for(V)), dim3(kThreads), 0, st, keysB, rbB, p.perm,
-                     p.row_seg_first, V, T, L.max_segments, p.seg_row, p.seg_beg, p.seg_end,
+  // segments per row in perm order, their cost, row blocks
+  const int64_t nst = L.scan_tiles_rows;
+  const Order ord = {{keysA, keysB}, {valsA, valsB}, {rbA, rbB}};
+  hipLaunchKernelGGL(k_seg_sums, dim3(nst), dim3(kSegTile), 0, st, ord, V, T, p.row_cost, tile_sums, nst,
                      p.counts);
-  // cost prefix over segments -> row blocks
-  scan(CostF{p.seg_beg, p.seg_end, p.row_cost}, L.max_segments, p.counts + kNumSegments, P,
-       nullptr, tile_sums, p.counts, st);
-  hipLaunchKernelGGL(k_blocks, dim3(grid_for(L.max_segments)), dim3(kThreads), 0, st, P,
-                     p.block_cost, L.max_segments, L.max_blocks, p.block_ptr, p.counts);
+  const int scanned = nst > kSumTiles ? 1 : 0;
+  if (scanned) {
+    hipLaunchKernelGGL(k_scan_tilesums, dim3(1), dim3(1024), 0, st, tile_sums, nst, 0, p.counts);
+    hipLaunchKernelGGL(k_scan_tilesums, dim3(1), dim3(1024), 0, st, tile_sums + nst, nst, 0,
+                       p.counts);
+  }
+  int bshift = -1;
+  for (int k = 0; k < 31; ++k)
+    if (p.block_cost == 1 << k) bshift = k;
+  hipLaunchKernelGGL(k_seg_emit, dim3(nst), dim3(kSegTile), 0, st, ord, V, T, p.row_cost, p.block_cost, bshift, tile_sums,
+                     nst, scanned, L.max_segments, L.max_blocks, p.perm, p.row_seg_first, p.seg_row,
+                     p.seg_beg, p.seg_end, p.block_ptr, p.counts);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && join) e = hipEventRecord(join, st);
   return e;

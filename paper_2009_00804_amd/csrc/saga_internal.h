@@ -28,7 +28,7 @@ struct PlanLayout {
   size_t off_d_in, off_d_out, off_perm, off_first, off_seg_row, off_seg_beg, off_seg_end,
       off_block_ptr, off_counts, off_scratch, scratch_bytes, total;
   int64_t max_segments, max_blocks, max_split, max_split_segments;
-  int64_t radix_tiles, scan_tiles_rows, scan_tiles_segs;
+  int64_t radix_tiles, scan_tiles_rows;
   int64_t outdeg_nb, edge_tiles;
   bool outdeg_bucketed;
 };
