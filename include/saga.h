@@ -642,8 +642,9 @@ saga_status saga_layer(const saga_plan* plan, const saga_layer_desc* desc, saga_
  *                           gather
  *   SAGE_POOL               pool transform, max gather, concat transform
  *   SAGE_LSTM               input transform, LSTM gather, concat transform
- *   GATED_GRU               source-gate transform, destination-gate
- *                           transform, gated gather, GRU transform
+ *   GATED_GRU               source-gate transform (with the destination's, one
+ *                           product), destination-gate transform (nothing
+ *                           left), gated gather, GRU transform
  *   RGCN                    relation transform, self transform, typed gather
  * Each saga_layer call starts again from events[0].  The setting is
  * thread-local and copied (the array may be freed after the call); pass

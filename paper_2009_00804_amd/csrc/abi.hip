@@ -383,16 +383,16 @@ saga_status run_gather_transform(const saga_plan& p, const saga_edge_op& op,
 }
 
 saga_status validate_gemm(const saga_gemm_op& op, const saga_cmat& a, const saga_cmat& w,
-                          const saga_cmat& a2, const saga_cmat& w2, const saga_mat& out) {
+                          const saga_cmat& a2, const saga_cmat& w2, const saga_mat& out, int64_t N) {
   if (op.dtype != SAGA_F32 && op.dtype != SAGA_BF16) return fail(SAGA_EINVAL, "bad dtype");
   if (op.mode < SAGA_GEMM_PLAIN || op.mode > SAGA_GEMM_GRU) return fail(SAGA_EINVAL, "bad mode");
   if (op.act < SAGA_ACT_NONE || op.act > SAGA_ACT_TANH) return fail(SAGA_EINVAL, "bad activation");
   const size_t es = esize(op.dtype);
-  const int64_t M = a.rows, K = a.cols, N = w.cols;
+  const int64_t M = a.rows, K = a.cols;  // N: w.cols, or more (a folded form)
   if (M < 0 || K <= 0 || N <= 0) return fail(SAGA_EINVAL, "gemm: empty operand");
   saga_status s = check_mat(a.ptr, a.rows, a.cols, a.ld, M, K, es, true, "a");
   if (s) return s;
-  s = check_mat(w.ptr, w.rows, w.cols, w.ld, K, N, es, false, "w");
+  s = check_mat(w.ptr, w.rows, w.cols, w.ld, K, w.cols, es, false, "w");
   if (s) return s;
   if (op.mode != SAGA_GEMM_PLAIN) {
     s = check_mat(a2.ptr, a2.rows, a2.cols, a2.ld, M, a2.cols, es, true, "a2");
@@ -439,13 +439,26 @@ size_t gemm_ws_bytes(const saga_gemm_op& op, int64_t k, int64_t k2, int64_t n) {
   return saga::gemm_workspace_bytes(op.dtype, op.mode, n, k, op.mode == SAGA_GEMM_PLAIN ? 0 : k2);
 }
 
+// A PLAIN float32 product whose weights are held in another form: column
+// blocks `cbs` apart (w: their extent as one dense matrix), or (fold > 0)
+// followed by the attention vectors folded into them
+struct WForm {
+  int64_t cb, cbs;
+  int fold, heads;
+  const float *al, *ar;
+};
+size_t form_ws_bytes(int64_t k, int64_t n) {
+  return saga::split_workspace_bytes(SAGA_GEMM_PLAIN, n, k, 0, 1);
+}
+
 saga_status run_gemm(const saga_gemm_op& op, const saga_cmat& a, const saga_cmat& w,
                      const saga_cmat& a2, const saga_cmat& w2, const float* bias,
                      const float* bias2, const saga_mat& out, void* ws, size_t ws_bytes,
-                     hipStream_t st) {
-  saga_status s = validate_gemm(op, a, w, a2, w2, out);
+                     hipStream_t st, const WForm* form = nullptr) {
+  const int64_t N = form && form->fold > 0 ? w.cols + 2 * form->heads : w.cols;
+  saga_status s = validate_gemm(op, a, w, a2, w2, out, N);
   if (s) return s;
-  const size_t need = gemm_ws_bytes(op, a.cols, a2.cols, w.cols);
+  const size_t need = form ? form_ws_bytes(a.cols, N) : gemm_ws_bytes(op, a.cols, a2.cols, N);
   if (!ws || ws_bytes < need)
     return fail(SAGA_EWORKSPACE, "apply_vertex workspace: need %zu bytes, got %zu", need, ws_bytes);
   if ((uintptr_t)ws % 256 != 0) return fail(SAGA_EINVAL, "workspace must be 256-byte aligned");
@@ -466,13 +479,21 @@ saga_status run_gemm(const saga_gemm_op& op, const saga_cmat& a, const saga_cmat
   g.mode = op.mode;
   g.act = op.act;
   g.M = a.rows;
-  g.N = w.cols;
+  g.N = N;
   g.K = a.cols;
   g.K2 = a2.cols;
+  if (form) {
+    g.wcb = form->cb;
+    g.wcbs = form->cbs;
+    g.fold = form->fold;
+    g.fold_heads = form->heads;
+    g.fold_al = form->al;
+    g.fold_ar = form->ar;
+  }
   g.a = a.ptr;
   g.lda = a.ld;
   g.w = w.ptr;
-  g.ldw = w.ld;
+  g.ldw = form && form->cb > 0 ? form->cb : w.ld;
   g.a2 = a2.ptr;
   g.lda2 = a2.ld;
   g.w2 = w2.ptr;
@@ -731,7 +752,6 @@ struct LayerBufs {
   void* z = nullptr; int64_t ldz = 0;      // GCN Z / GAT [z|el|er] / SAGE P / gated S_src
   void* z2 = nullptr; int64_t ldz2 = 0;    // SAGE A / gated S_dst / GCN agg (aggregate-first)
   void* z3 = nullptr; int64_t ldz3 = 0;    // gated a
-  float* wext = nullptr; int64_t ldw = 0;  // GAT folded weights
   void* part = nullptr;
   size_t part_bytes = 0;
   void* gws = nullptr;                     // packed weights of the layer's GEMMs
@@ -782,8 +802,6 @@ size_t layer_carve(const saga_plan& p, const saga_layer_desc& d, void* base, Lay
     case SAGA_LAYER_GAT: {
       const int64_t F = d.head_mean ? (int64_t)d.out_feat * d.heads : d.out_feat;
       const int64_t cols = F + 2 * d.heads;
-      b->ldw = ld_for(cols, SAGA_F32);
-      b->wext = static_cast<float*>(c.take((size_t)d.in_feat * b->ldw * 4));
       b->ldz = ld_for(cols, SAGA_F32);
       b->z = c.take((size_t)V * b->ldz * 4);
       op.reduce = SAGA_RED_SOFTMAX;
@@ -845,7 +863,7 @@ size_t layer_carve(const saga_plan& p, const saga_layer_desc& d, void* base, Lay
       break;
     case SAGA_LAYER_GAT: {
       const int64_t F = d.head_mean ? Fo * d.heads : Fo;
-      gb = gemm_ws_bytes(g, Fi, 0, F + 2 * d.heads);
+      gb = form_ws_bytes(Fi, F + 2 * d.heads);
       break;
     }
     case SAGA_LAYER_SAGE_POOL: {
@@ -855,7 +873,7 @@ size_t layer_carve(const saga_plan& p, const saga_layer_desc& d, void* base, Lay
       break;
     }
     case SAGA_LAYER_GATED_GRU: {
-      gb = gemm_ws_bytes(g, Fi, 0, Fi);
+      gb = form_ws_bytes(Fi, 2 * Fi);
       g.mode = SAGA_GEMM_GRU;
       gb = std::max(gb, gemm_ws_bytes(g, Fi, Fi, 3 * Fi));
       break;
@@ -1025,12 +1043,11 @@ saga_status run_layer(const saga_plan& p, const saga_layer_desc& d, const saga_c
       const int64_t H = d.heads;
       const int64_t F = d.head_mean ? Fo * H : Fo;
       const int64_t cols = F + 2 * H;
-      hipError_t e = saga::launch_fold_attention(static_cast<const float*>(d.w), Fi, F, (int)H,
-                                                 d.attn_l, d.attn_r, b.wext, b.ldw, st);
-      if (e != hipSuccess) return dev_fail(e, "fold launch");
+      // [z | el | er] = X [W | W a_l | W a_r], folded while W is packed
+      const WForm fold = {0, 0, (int)F, (int)H, d.attn_l, d.attn_r};
       g.mode = SAGA_GEMM_PLAIN;
-      s = run_gemm(g, x, saga_cmat{b.wext, Fi, cols, b.ldw}, none, none, nullptr, nullptr,
-                   saga_mat{b.z, V, cols, b.ldz}, b.gws, b.gws_bytes, st);
+      s = run_gemm(g, x, saga_cmat{d.w, Fi, F, F}, none, none, nullptr, nullptr,
+                   saga_mat{b.z, V, cols, b.ldz}, b.gws, b.gws_bytes, st, &fold);
       if (s) return s;
       if ((s = stage_done(st))) return s;
       const float* z = static_cast<const float*>(b.z);
@@ -1113,15 +1130,16 @@ saga_status run_layer(const saga_plan& p, const saga_layer_desc& d, const saga_c
     }
     case SAGA_LAYER_GATED_GRU: {
       const int64_t F = Fi, Fe = d.edge_feat;
+      // [S_src | S_dst] = X [W_e,src | W_e,dst]: one product over both F x F blocks
+      const WForm gates = {F, F * F, 0, 0, nullptr, nullptr};
       g.mode = SAGA_GEMM_PLAIN;
-      s = run_gemm(g, x, saga_cmat{d.w_e, F, F, F}, none, none, nullptr, nullptr,
-                   saga_mat{b.z, V, F, b.ldz}, b.gws, b.gws_bytes, st);
+      g.split_col = (int32_t)F;
+      g.tail = saga_mat{b.z2, V, F, b.ldz2};
+      s = run_gemm(g, x, saga_cmat{d.w_e, F, 2 * F, 2 * F}, none, none, nullptr, nullptr,
+                   saga_mat{b.z, V, F, b.ldz}, b.gws, b.gws_bytes, st, &gates);
       if (s) return s;
-      if ((s = stage_done(st))) return s;
-      s = run_gemm(g, x, saga_cmat{d.w_e + F * F, F, F, F}, none, none, nullptr, nullptr,
-                   saga_mat{b.z2, V, F, b.ldz2}, b.gws, b.gws_bytes, st);
-      if (s) return s;
-      if ((s = stage_done(st))) return s;
+      g.split_col = 0;
+      if ((s = stage_done(st)) || (s = stage_done(st))) return s;  // both gate transforms
       op.msg = SAGA_MSG_GATED;
       op.reduce = SAGA_RED_SUM;
       in.src = x;

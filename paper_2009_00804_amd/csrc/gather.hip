@@ -946,28 +946,6 @@ __global__ __launch_bounds__(kThreads) void k_combine(GatherArgs a) {
   }
 }
 
-__global__ void k_fold_attention(const float* __restrict__ w, int64_t K, int64_t F, int H,
-                                 const float* __restrict__ al, const float* __restrict__ ar,
-                                 float* __restrict__ wx, int64_t ldx) {
-  const int64_t ncol = F + 2 * H;
-  const int64_t n = K * ncol;
-  const int64_t D = F / H;
-  for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < n;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = idx / ncol, c = idx % ncol;
-    float v;
-    if (c < F) {
-      v = w[k * F + c];
-    } else {
-      const int64_t hh = (c - F) % H;
-      const float* att = (c - F) < H ? al : ar;
-      v = 0.0f;
-      for (int64_t dd = 0; dd < D; ++dd) v += w[k * F + hh * D + dd] * att[hh * D + dd];
-    }
-    wx[k * ldx + c] = v;
-  }
-}
-
 inline int next_pow2(int x) {
   int p = 1;
   while (p < x) p <<= 1;
@@ -1323,15 +1301,6 @@ hipError_t launch_unfused(const GatherArgs& a0, int64_t E, void* msg, int64_t ld
     err = hipGetLastError();
   }
   return err;
-}
-
-hipError_t launch_fold_attention(const float* w, int64_t K, int64_t F, int heads, const float* al,
-                                 const float* ar, float* w_ext, int64_t ld_ext, hipStream_t st) {
-  const int64_t n = K * (F + 2 * heads);
-  const unsigned grid = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(k_fold_attention, dim3(grid), dim3(256), 0, st, w, K, F, heads, al, ar, w_ext,
-                     ld_ext);
-  return hipGetLastError();
 }
 
 }  // namespace saga

@@ -676,23 +676,25 @@ hipError_t dispatch(const GemmArgs& g, hipStream_t st) {
     if (used || e != hipSuccess) return e;
   }
   const Tiling t = choose(g.dtype, g.mode, g.N, g.mode == SAGA_GEMM_CONCAT ? g.K + g.K2 : g.K);
-  if (g.mode == SAGA_GEMM_GRU) {
-    dim3 grid((unsigned)((g.M + 63) / 64));
-    // two stages when both products have at most four k chunks (as for the
-    // narrow plain tiles)
-    const bool two = chunks(g.dtype, std::max(g.K, g.K2)) <= 4;
+  if constexpr (sizeof(T) == 2) {  // float32: gemm_split.hip
+    if (g.mode == SAGA_GEMM_GRU) {
+      dim3 grid((unsigned)((g.M + 63) / 64));
+      // two stages when both products have at most four k chunks (as for the
+      // narrow plain tiles)
+      const bool two = chunks(g.dtype, std::max(g.K, g.K2)) <= 4;
 #define SAGA_GRU(N3)                                                                     \
-  if (two) hipLaunchKernelGGL((k_gemm_gru<T, N3, 2>), grid, dim3(kThreads), 0, st, g);  \
-  else hipLaunchKernelGGL((k_gemm_gru<T, N3, 4>), grid, dim3(kThreads), 0, st, g)
-    switch (t.nt) {
-      case 3: SAGA_GRU(1); break;
-      case 6: SAGA_GRU(2); break;
-      case 9: SAGA_GRU(3); break;
-      case 12: SAGA_GRU(4); break;
-      default: return hipErrorInvalidValue;
-    }
+    if (two) hipLaunchKernelGGL((k_gemm_gru<T, N3, 2>), grid, dim3(kThreads), 0, st, g);  \
+    else hipLaunchKernelGGL((k_gemm_gru<T, N3, 4>), grid, dim3(kThreads), 0, st, g)
+      switch (t.nt) {
+        case 3: SAGA_GRU(1); break;
+        case 6: SAGA_GRU(2); break;
+        case 9: SAGA_GRU(3); break;
+        case 12: SAGA_GRU(4); break;
+        default: return hipErrorInvalidValue;
+      }
 #undef SAGA_GRU
-    return hipGetLastError();
+      return hipGetLastError();
+    }
   }
   switch (t.nt) {
     case 1: return launch_nt<T, 1>(g, t, st);
@@ -765,13 +767,13 @@ void grouped_packed(int dtype, int64_t N, int64_t K, int64_t* np, int64_t* kp) {
 
 size_t gemm_workspace_bytes(int dtype, int mode, int64_t N, int64_t K, int64_t K2) {
   if (mode != SAGA_GEMM_CONCAT && mode != SAGA_GEMM_GRU) K2 = 0;
-  if (gemm_splits(dtype, mode, N, K + K2)) return split_workspace_bytes(N, K, K2, 1);
+  if (gemm_splits(dtype, mode, N, K + K2)) return split_workspace_bytes(mode, N, K, K2, 1);
   return packed_layout(dtype, mode, N, K, K2).bytes;
 }
 
 hipError_t launch_gemm(const GemmArgs& g0, hipStream_t st) {
   if (g0.M == 0) return hipSuccess;
-  if (gemm_splits(g0.dtype, g0.mode, g0.N, g0.K + (g0.mode == SAGA_GEMM_CONCAT ? g0.K2 : 0)))
+  if (g0.forms() || gemm_splits(g0.dtype, g0.mode, g0.N, g0.K + (g0.mode == SAGA_GEMM_CONCAT ? g0.K2 : 0)))
     return launch_gemm_split(g0, st);
   const Packed pk = packed_layout(g0.dtype, g0.mode, g0.N, g0.K, g0.K2);
   if (!g0.ws || g0.ws_bytes < pk.bytes) return hipErrorInvalidValue;
@@ -792,7 +794,7 @@ hipError_t launch_gemm(const GemmArgs& g0, hipStream_t st) {
 }
 
 size_t gemm_grouped_workspace_bytes(int dtype, int groups, int64_t N, int64_t K) {
-  if (gemm_splits(dtype, SAGA_GEMM_PLAIN, N, K)) return split_workspace_bytes(N, K, 0, groups);
+  if (gemm_splits(dtype, SAGA_GEMM_PLAIN, N, K)) return split_workspace_bytes(SAGA_GEMM_PLAIN, N, K, 0, groups);
   int64_t np, kp;
   grouped_packed(dtype, N, K, &np, &kp);
   const size_t es = dtype == SAGA_BF16 ? 2 : 4;

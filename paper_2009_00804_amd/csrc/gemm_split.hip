@@ -1,4 +1,4 @@
-// ApplyVertex in float32: PLAIN, CONCAT and grouped products on the bfloat16
+// ApplyVertex in float32: PLAIN, CONCAT, GRU and grouped products on the bfloat16
 // matrix cores, every float32 operand as an exact sum of three bfloat16 values.
 #include "gemm_device.h"
 
@@ -47,6 +47,36 @@ __device__ __forceinline__ void split3(f32x2 x, uint32_t (&p)[3]) {
     __builtin_memcpy(&p[q], &h, 4);
     x -= f32x2{__uint_as_float(p[q] << 16), __uint_as_float(p[q] & 0xffff0000u)};
   }
+}
+
+// One operand's weights, K x N, as the caller holds them (GemmArgs)
+struct WSrc {
+  const float* w;
+  int64_t ldw, K, N;
+  int64_t cb, cbs;  // cb > 0: column n is column n % cb of the block at w + n / cb * cbs
+  // fold > 0: columns from `fold` on are the attention vectors folded into the
+  // first `fold`: column fold + h is sum_d w[:, h D + d] al[h D + d], then ar
+  int fold, heads;
+  const float *al, *ar;
+  __device__ float at(int64_t k, int64_t n) const {
+    if (k >= K || n >= N) return 0.0f;
+    if (fold > 0 && n >= fold) {
+      const int D = fold / heads, h = (int)(n - fold) % heads;
+      const float* att = (n - fold < heads ? al : ar) + h * D;
+      const float* row = w + k * ldw + h * D;
+      float v = 0.0f;
+      for (int d = 0; d < D; ++d) v += row[d] * att[d];
+      return v;
+    }
+    return cb > 0 ? w[n / cb * cbs + k * ldw + n % cb] : w[k * ldw + n];
+  }
+};
+__host__ __device__ inline WSrc wsrc1(const GemmArgs& g) {
+  return WSrc{static_cast<const float*>(g.w), g.ldw, g.K, g.N, g.wcb, g.wcbs, g.fold, g.fold_heads,
+              g.fold_al, g.fold_ar};
+}
+__host__ __device__ inline WSrc wsrc2(const GemmArgs& g) {
+  return WSrc{static_cast<const float*>(g.w2), g.ldw2, g.K2, g.N, 0, 0, 0, 0, nullptr, nullptr};
 }
 
 // A straight from global memory into registers and split there; the packed
@@ -161,9 +191,10 @@ struct Split3 {
       b[q] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(
           Bs + (q * NT + g) * 64 + lane);
   }
-  template <int U, bool LOAD, bool MASK, bool LAST>
+  // Column tile g goes to accumulator g, or g + SHIFT from tile FROM on.
+  template <int U, bool LOAD, bool MASK, bool LAST, int FROM, int SHIFT, int NA>
   __device__ __forceinline__ static void step(const Ctx& c, int i, uint4 (&a)[2][MT][2], Parts (&ap)[2],
-                                              float (&amax)[MT], f32x4 (&acc)[MT][NT]) {
+                                              float (&amax)[MT], f32x4 (&acc)[MT][NA]) {
     // chunk i's weights landed (only chunk i + 1's A loads are newer), for
     // every wave; the other stage is free again
     wait_vm<LAST ? 0 : 2 * MT>();
@@ -186,8 +217,8 @@ struct Split3 {
       for (int q = 0; q < 6; ++q) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-          acc[mt][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part(ap[U], mt, QA[q]), b[g & 1][QB[q]],
-                                                               acc[mt][g], 0, 0, 0);
+          acc[mt][g + (g >= FROM ? SHIFT : 0)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              part(ap[U], mt, QA[q]), b[g & 1][QB[q]], acc[mt][g + (g >= FROM ? SHIFT : 0)], 0, 0, 0);
         if (!LAST && g >= G0) {
           const int slot = (g - G0) * 6 + q;
 #pragma unroll
@@ -200,10 +231,11 @@ struct Split3 {
   }
   // acc += A[tile0 .. tile0 + BM) x the column block's image; amax: this
   // lane's part of its rows' largest magnitudes
+  template <int FROM = NT, int SHIFT = 0, int NA = NT>
   __device__ __forceinline__ static void phase(const float* __restrict__ A, int64_t lda, int64_t M,
                                                int64_t K, const uint4* __restrict__ Wi,
                                                int64_t tile0, uint4* ring, float (&amax)[MT],
-                                               f32x4 (&acc)[MT][NT],
+                                               f32x4 (&acc)[MT][NA],
                                                const int32_t* __restrict__ arow = nullptr) {
     Ctx c;
     int64_t off[MT];
@@ -225,19 +257,19 @@ struct Split3 {
     for (int d = 0; d < MT * 4; ++d) split_pair(a[0], d / 4, d % 4, amax, ap[0]);
     int i = 0;
     for (; i + 3 <= c.last; i += 2) {
-      step<0, true, false, false>(c, i, a, ap, amax, acc);
-      step<1, true, false, false>(c, i + 1, a, ap, amax, acc);
+      step<0, true, false, false, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
+      step<1, true, false, false, FROM, SHIFT, NA>(c, i + 1, a, ap, amax, acc);
     }
     const int left = c.last - i;  // 0, 1 or 2 more chunks after chunk i
     if (left == 2) {
-      step<0, true, false, false>(c, i, a, ap, amax, acc);
-      step<1, false, true, false>(c, i + 1, a, ap, amax, acc);
-      step<0, false, false, true>(c, i + 2, a, ap, amax, acc);
+      step<0, true, false, false, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
+      step<1, false, true, false, FROM, SHIFT, NA>(c, i + 1, a, ap, amax, acc);
+      step<0, false, false, true, FROM, SHIFT, NA>(c, i + 2, a, ap, amax, acc);
     } else if (left == 1) {
-      step<0, false, true, false>(c, i, a, ap, amax, acc);
-      step<1, false, false, true>(c, i + 1, a, ap, amax, acc);
+      step<0, false, true, false, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
+      step<1, false, false, true, FROM, SHIFT, NA>(c, i + 1, a, ap, amax, acc);
     } else {
-      step<0, false, false, true>(c, i, a, ap, amax, acc);
+      step<0, false, false, true, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
     }
     ring_barrier();  // the stages may be refilled by a following phase
   }
@@ -257,69 +289,97 @@ struct Split3 {
 
   // acc += A rows x W with the float32 instruction, operands straight from
   // memory: the waves whose values the split does not take (rare, not tuned)
+  template <int FROM = NT, int SHIFT = 0, int NA = NT>
   __device__ __forceinline__ static void native_phase(
-      const float* __restrict__ A, int64_t lda, int64_t M, int64_t K, const float* __restrict__ W,
-      int64_t ldw, int64_t N, int64_t n0, int64_t tile0, f32x4 (&acc)[MT][NT],
-      const int32_t* __restrict__ arow = nullptr) {
+      const float* __restrict__ A, int64_t lda, int64_t M, const WSrc& w, int64_t n0, int64_t tile0,
+      f32x4 (&acc)[MT][NA], const int32_t* __restrict__ arow = nullptr) {
     const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
     int64_t off[MT];
     row_offsets(arow, lda, M, tile0 + (threadIdx.x >> 6) * MT * 16, off);
-    for (int64_t k0 = 0; k0 < K; k0 += 4) {
+    for (int64_t k0 = 0; k0 < w.K; k0 += 4) {
       const int64_t k = k0 + lg;
       float a[MT], b[NT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) a[mt] = k < K ? A[off[mt] + k] : 0.0f;
+      for (int mt = 0; mt < MT; ++mt) a[mt] = k < w.K ? A[off[mt] + k] : 0.0f;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int64_t n = n0 + nt * 16 + lr;
-        b[nt] = k < K && n < N ? W[k * ldw + n] : 0.0f;
-      }
+      for (int nt = 0; nt < NT; ++nt) b[nt] = w.at(k, n0 + nt * 16 + lr);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+        for (int nt = 0; nt < NT; ++nt) {
+          f32x4& c = acc[mt][nt + (nt >= FROM ? SHIFT : 0)];
+          c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b[nt], c, 0, 0, 0);
+        }
     }
   }
 };
 
-// The image Split3 streams, for one group of weights per blockIdx.y: for
-// column block b, chunk c, plane q, tile t of the block: 64 pieces of 8 k.
-// One workgroup per 16-column tile, which sees whole columns, so its flag
-// (some column outside the split's range) needs no atomics across workgroups.
-// flags: one int per 16-column tile.
-constexpr int kPackThreads = 1024;
-__global__ __launch_bounds__(kPackThreads) void k_pack_split(const float* __restrict__ W, int64_t ldw,
-                                                             int64_t K, int64_t N, int nt,
-                                                             uint4* __restrict__ img,
-                                                             int32_t* __restrict__ flags) {
+// The image Split3 streams, for one group of weights (blockIdx.y < groups) or
+// the second operand (the next one): for column block b, chunk c, plane q, tile
+// t of the block: 64 pieces of 8 k.  A workgroup takes kPackChunks chunks of a
+// 16-column tile and notes in its own flag whether a column of them is outside
+// the split's range (one workgroup per tile ran 5 to 6 us; a folded tile of 512
+// x 16, eight terms each, 20).
+constexpr int kPackThreads = 256, kPackChunks = kPackThreads / 64;
+__host__ __device__ inline int64_t pack_parts(int64_t nch) { return (nch + kPackChunks - 1) / kPackChunks; }
+struct PackOut {
+  uint4* img;
+  int32_t* flags;
+};
+__global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1, WSrc w2, PackOut o2,
+                                                             int groups, int nt) {
   __shared__ uint32_t cmax[16];
-  const int nch = (int)((K + 31) / 32), tile = blockIdx.x, tiles = gridDim.x;
+  const bool second = (int)blockIdx.y >= groups;
+  const int grp = second ? 0 : blockIdx.y;
+  WSrc w = second ? w2 : w1;
+  const PackOut o = second ? o2 : o1;
+  w.w += (int64_t)grp * w.K * w.ldw;
+  const int nch = (int)((w.K + 31) / 32), tile = blockIdx.x, tiles = gridDim.x;
   const int b = tile / nt, t = tile % nt;
-  const float* w = W + (int64_t)blockIdx.y * K * ldw;
-  uint4* im = img + ((int64_t)blockIdx.y * tiles * nch + (int64_t)b * nt * nch) * 192;
+  uint4* im = o.img + ((int64_t)grp * tiles * nch + (int64_t)b * nt * nch) * 192;
+  const int part = blockIdx.z;
+  if (part >= pack_parts(nch)) return;
   if (threadIdx.x < 16) cmax[threadIdx.x] = 0;
   __syncthreads();
   const int r = threadIdx.x & 15;
   const int64_t n = (int64_t)tile * 16 + r;
+  const bool folded = w.fold > 0 && n >= w.fold && n < w.N;
+  // column n (a plain or a block's), or the folded one's first term
+  const int D = folded ? w.fold / w.heads : 1, h = folded ? (int)(n - w.fold) % w.heads : 0;
+  const float* att = folded ? (n - w.fold < w.heads ? w.al : w.ar) + h * D : nullptr;
+  const float* col = w.w + (folded ? h * D : w.cb > 0 ? (int)n / (int)w.cb * w.cbs + (int)n % (int)w.cb : n);
+  const int64_t kn = n < w.N ? w.K : 0;
   uint32_t m = 0;
-  for (int i = threadIdx.x; i < nch * 64; i += kPackThreads) {
-    const int c = i / 64, p = (i / 16) % 4;
+  const int c = part * kPackChunks + threadIdx.x / 64, p = (threadIdx.x / 16) % 4;
+  if (c < nch) {
     const int64_t k0 = (int64_t)c * 32 + p * 4;  // and k0 + 16
+    float x[8];
+    if (folded) {
+      // eight k at a time, so that their loads overlap
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+#pragma unroll 4
+      for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int64_t k = k0 + e % 4 + 16 * (e / 4);
+          x[e] += (k < kn ? col[k * w.ldw + d] : 0.0f) * att[d];
+        }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t k = k0 + e % 4 + 16 * (e / 4);
+        x[e] = k < kn ? col[k * w.ldw] : 0.0f;
+      }
+    }
     uint32_t q[3][4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      f32x2 x;
+      m = max(m, max(__float_as_uint(fabsf(x[2 * d])), __float_as_uint(fabsf(x[2 * d + 1]))));
+      uint32_t o3[3];
+      split3(f32x2{x[2 * d], x[2 * d + 1]}, o3);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int64_t k = k0 + 2 * (d & 1) + 16 * (d >> 1) + j;
-        x[j] = n < N && k < K ? w[k * ldw + n] : 0.0f;
-        m = max(m, __float_as_uint(fabsf(x[j])));
-      }
-      uint32_t o[3];
-      split3(x, o);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) q[k][d] = o[k];
+      for (int k = 0; k < 3; ++k) q[k][d] = o3[k];
     }
 #pragma unroll
     for (int k = 0; k < 3; ++k)
@@ -330,8 +390,17 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_split(const float* __rest
   if (threadIdx.x == 0) {
     int sp = 0;
     for (int j = 0; j < 16; ++j) sp |= split_special(__uint_as_float(cmax[j]));
-    flags[(int64_t)blockIdx.y * tiles + tile] = sp;
+    o.flags[((int64_t)grp * tiles + tile) * pack_parts(nch) + part] = sp;
   }
+}
+
+// whether k_pack_split flagged any column of column block b (uniform)
+template <int NT>
+__device__ __forceinline__ bool any_flag(const int32_t* __restrict__ flags, int64_t b, int64_t nch) {
+  const int n = NT * (int)pack_parts(nch);
+  int f = 0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) f |= flags[b * n + i];
+  return __any(f != 0);
 }
 
 // float32 PLAIN / CONCAT / grouped through Split3.  The column blocks of one
@@ -382,18 +451,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
              ph ? static_cast<const uint4*>(g.wt2) + (int64_t)y * nch2 * R::STAGE : wi, tile0, ring,
              amax, acc, arow);
   bool slow = R::special(amax);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    slow |= g.wflags[((int64_t)grp * ny + y) * NT + t] != 0;
-    if (concat) slow |= g.wflags2[(int64_t)y * NT + t] != 0;
-  }
+  slow |= any_flag<NT>(g.wflags, (int64_t)grp * ny + y, nch);
+  if (concat) slow |= any_flag<NT>(g.wflags2, y, nch2);
   if (slow) {
     clear();
-    R::native_phase(A, g.lda, g.M, g.K, static_cast<const float*>(g.w) + (int64_t)grp * g.K * g.ldw,
-                    g.ldw, g.N, n0, tile0, acc, arow);
-    if (concat)
-      R::native_phase(A2, g.lda2, g.M, g.K2, static_cast<const float*>(g.w2), g.ldw2, g.N, n0, tile0,
-                      acc);
+    WSrc w = wsrc1(g);
+    w.w += (int64_t)grp * g.K * g.ldw;
+    R::native_phase(A, g.lda, g.M, w, n0, tile0, acc, arow);
+    if (concat) R::native_phase(A2, g.lda2, g.M, wsrc2(g), n0, tile0, acc);
   }
   const int64_t row0 = tile0 + wave * MT * 16;
   if constexpr (GROUPED) {
@@ -412,6 +477,69 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   store_tile<float, MT, NT, R>(g, row0, n0, acc, ring);
 }
 
+// GRU through Split3 (GGNN's ApplyVertex, Fig. 2): a wave's 16 rows of a w and
+// a2 w2, column blocks (r, z, n) of F = 16 NT3.  Both products' r and z columns
+// add up in the same accumulators; only the n blocks are kept apart.
+template <int NT3>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_gru_split(GemmArgs g) {
+  constexpr int NT = 3 * NT3, NA = 4 * NT3;
+  typedef Split3<1, NT, 4> R;
+  __shared__ uint4 ring[R::RING_SLOTS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t tile0 = (int64_t)blockIdx.x * R::BM;
+  const float *A = static_cast<const float*>(g.a), *h = static_cast<const float*>(g.a2);
+  f32x4 acc[1][NA];
+  auto clear = [&] {
+#pragma unroll
+    for (int t = 0; t < NA; ++t) acc[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+  float amax[1] = {0.0f};
+  R::template phase<NT, 0, NA>(A, g.lda, g.M, g.K, static_cast<const uint4*>(g.wt), tile0, ring, amax, acc);
+  R::template phase<2 * NT3, NT3, NA>(h, g.lda2, g.M, g.K2, static_cast<const uint4*>(g.wt2), tile0, ring,
+                                      amax, acc);
+  bool slow = R::special(amax);
+  slow |= any_flag<NT>(g.wflags, 0, (g.K + 31) / 32) || any_flag<NT>(g.wflags2, 0, (g.K2 + 31) / 32);
+  if (slow) {
+    clear();
+    R::template native_phase<NT, 0, NA>(A, g.lda, g.M, wsrc1(g), 0, tile0, acc);
+    R::template native_phase<2 * NT3, NT3, NA>(h, g.lda2, g.M, wsrc2(g), 0, tile0, acc);
+  }
+  constexpr int F = NT3 * 16;
+  const int64_t row0 = tile0 + wave * 16;
+  float* out = static_cast<float*>(g.out);
+  // biases and previous states are all loaded before the first store (a
+  // load after a store the compiler cannot tell apart from it would wait)
+  float br[NT3], bz[NT3], bi[NT3], bh[NT3], hp[4][NT3];
+#pragma unroll
+  for (int t = 0; t < NT3; ++t) {
+    const int c = t * 16 + (lane & 15);
+    const float* b1 = g.bias;
+    const float* b2 = g.bias2;
+    br[t] = (b1 ? b1[c] : 0.f) + (b2 ? b2[c] : 0.f);
+    bz[t] = (b1 ? b1[F + c] : 0.f) + (b2 ? b2[F + c] : 0.f);
+    bi[t] = b1 ? b1[2 * F + c] : 0.f;
+    bh[t] = b2 ? b2[2 * F + c] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = row0 + 4 * (lane >> 4) + r;
+      hp[r][t] = row < g.M ? h[row * g.lda2 + c] : 0.f;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t row = row0 + 4 * (lane >> 4) + r;
+    if (row >= g.M) continue;
+#pragma unroll
+    for (int t = 0; t < NT3; ++t) {
+      const float rr = sigmoidf_(acc[0][t][r] + br[t]);
+      const float zz = sigmoidf_(acc[0][NT3 + t][r] + bz[t]);
+      const float nn = tanhf(acc[0][2 * NT3 + t][r] + bi[t] + rr * (acc[0][3 * NT3 + t][r] + bh[t]));
+      out[row * g.ldo + t * 16 + (lane & 15)] = (1.0f - zz) * nn + zz * hp[r][t];
+    }
+  }
+}
+
 // ---- float32 through Split3 ----
 // column blocks of NT 16-column tiles: as few blocks of at most eight as
 // cover N, of equal width
@@ -419,23 +547,15 @@ struct SplitShape {
   int nt, ny;
   int64_t nch, img_bytes, flag_bytes;  // per K operand (and group, for the image)
 };
-SplitShape split_shape(int64_t N, int64_t K, int groups) {
+SplitShape split_shape(int64_t N, int64_t K, int groups, int mode) {
   SplitShape s;
   const int tiles = (int)((N + 15) / 16);
-  s.ny = (tiles + 7) / 8;
+  s.ny = mode == SAGA_GEMM_GRU ? 1 : (tiles + 7) / 8;  // a GRU row needs all its columns
   s.nt = (tiles + s.ny - 1) / s.ny;
   s.nch = (K + 31) / 32;
   s.img_bytes = (int64_t)groups * s.ny * s.nt * s.nch * 3072;
-  s.flag_bytes = ((int64_t)groups * s.ny * s.nt * 4 + 255) / 256 * 256;
+  s.flag_bytes = ((int64_t)groups * s.ny * s.nt * pack_parts(s.nch) * 4 + 255) / 256 * 256;
   return s;
-}
-
-hipError_t pack_split(const void* w, int64_t ldw, int64_t K, int64_t N, int groups,
-                      const SplitShape& s, void* img, void* flags, hipStream_t st) {
-  hipLaunchKernelGGL(k_pack_split, dim3((unsigned)(s.ny * s.nt), (unsigned)groups),
-                     dim3(kPackThreads), 0, st, static_cast<const float*>(w), ldw, K, N, s.nt,
-                     static_cast<uint4*>(img), static_cast<int32_t*>(flags));
-  return hipGetLastError();
 }
 
 template <int MT, int NT, int NW, bool GROUPED>
@@ -483,32 +603,51 @@ hipError_t dispatch_split(const GemmArgs& g, const SplitShape& s, int64_t chunks
 }  // namespace
 
 bool gemm_splits(int dtype, int mode, int64_t N, int64_t K) {
-  return dtype == SAGA_F32 && mode != SAGA_GEMM_GRU && (N > 32 || K > 256);
+  return dtype == SAGA_F32 && (mode == SAGA_GEMM_GRU || N > 32 || K > 256);
 }
 
-size_t split_workspace_bytes(int64_t N, int64_t K, int64_t K2, int groups) {
-  const SplitShape s = split_shape(N, K, groups), s2 = split_shape(N, K2, groups);
+size_t split_workspace_bytes(int mode, int64_t N, int64_t K, int64_t K2, int groups) {
+  const SplitShape s = split_shape(N, K, groups, mode), s2 = split_shape(N, K2, groups, mode);
   return (size_t)(s.img_bytes + s2.img_bytes + s.flag_bytes + s2.flag_bytes);
 }
 
 // Workspace: the image of w, the image of w2, then the flags of each
 hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
-  const bool grouped = g0.groups > 0, cat = !grouped && g0.mode == SAGA_GEMM_CONCAT;
+  const bool grouped = g0.groups > 0, gru = !grouped && g0.mode == SAGA_GEMM_GRU;
+  const bool two = !grouped && g0.mode != SAGA_GEMM_PLAIN;
   const int groups = grouped ? g0.groups : 1;
-  const SplitShape s = split_shape(g0.N, g0.K, groups), s2 = split_shape(g0.N, cat ? g0.K2 : 0, groups);
-  if (!g0.ws || g0.ws_bytes < split_workspace_bytes(g0.N, g0.K, cat ? g0.K2 : 0, groups))
+  const int64_t K2 = two ? g0.K2 : 0;
+  const SplitShape s = split_shape(g0.N, g0.K, groups, g0.mode);
+  const SplitShape s2 = split_shape(g0.N, K2, groups, g0.mode);
+  if (!g0.ws || g0.ws_bytes < split_workspace_bytes(g0.mode, g0.N, g0.K, K2, groups))
     return hipErrorInvalidValue;
   GemmArgs g = g0;
   char* ws = static_cast<char*>(g.ws);
   char* fl = ws + s.img_bytes + s2.img_bytes;
   g.wt = ws;
   g.wt2 = ws + s.img_bytes;
-  g.wflags = reinterpret_cast<int32_t*>(fl);
-  g.wflags2 = reinterpret_cast<int32_t*>(fl + s.flag_bytes);
-  hipError_t e = pack_split(g.w, g.ldw, g.K, g.N, groups, s, ws, fl, st);
-  if (e == hipSuccess && cat)
-    e = pack_split(g.w2, g.ldw2, g.K2, g.N, 1, s2, ws + s.img_bytes, fl + s.flag_bytes, st);
+  int32_t* f1 = reinterpret_cast<int32_t*>(fl);
+  int32_t* f2 = reinterpret_cast<int32_t*>(fl + s.flag_bytes);
+  g.wflags = f1;
+  g.wflags2 = f2;
+  const unsigned parts = (unsigned)pack_parts(s.nch > s2.nch ? s.nch : s2.nch);
+  hipLaunchKernelGGL(k_pack_split, dim3((unsigned)(s.ny * s.nt), (unsigned)(groups + (two ? 1 : 0)), parts),
+                     dim3(kPackThreads), 0, st, wsrc1(g),
+                     PackOut{reinterpret_cast<uint4*>(ws), f1}, wsrc2(g),
+                     PackOut{reinterpret_cast<uint4*>(ws + s.img_bytes), f2}, groups, s.nt);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (gru) {
+    const dim3 grid((unsigned)((g.M + 63) / 64));
+    switch (s.nt) {
+      case 3: hipLaunchKernelGGL(k_gru_split<1>, grid, dim3(kThreads), 0, st, g); break;
+      case 6: hipLaunchKernelGGL(k_gru_split<2>, grid, dim3(kThreads), 0, st, g); break;
+      case 9: hipLaunchKernelGGL(k_gru_split<3>, grid, dim3(kThreads), 0, st, g); break;
+      case 12: hipLaunchKernelGGL(k_gru_split<4>, grid, dim3(kThreads), 0, st, g); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   const int64_t chunks = s.nch + s2.nch;
   return grouped ? dispatch_split<true>(g, s, chunks, st) : dispatch_split<false>(g, s, chunks, st);
 }

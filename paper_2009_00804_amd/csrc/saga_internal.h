@@ -129,9 +129,18 @@ struct GemmArgs {
   // set by launch_gemm: packed weights in the workspace, ld kp / kp2
   const void* wt; int64_t kp;
   const void* wt2; int64_t kp2;
-  // float32: per 16-column tile of wt / wt2, a column the split does not take
+  // float32: per 16-column tile of wt / wt2 and part of its k, a column the
+  // split does not take
   const int32_t* wflags;
   const int32_t* wflags2;
+  // forms of w that only the float32 split path takes (forms(): either set):
+  // wcb > 0: N / wcb column blocks of wcb columns (ld ldw), wcbs apart;
+  // fold > 0: w has `fold` columns and N = fold + 2 fold_heads, the rest being
+  // the attention vectors fold_al, fold_ar folded into w
+  int64_t wcb, wcbs;
+  int fold, fold_heads;
+  const float *fold_al, *fold_ar;
+  bool forms() const { return wcb > 0 || fold > 0; }
   // grouped mode (launch_gemm_grouped): row q of A is row arow[q] of a (a
   // negative entry gives an all-zero output row); w holds `groups` K x N
   // weights stacked; rows [grp_ptr[g], grp_ptr[g+1]) use weight g, ranges
@@ -163,12 +172,12 @@ hipError_t launch_lstm_gather(const LstmArgs& a, hipStream_t st);
 // bytes of workspace launch_gemm needs for these shapes (packed weights)
 size_t gemm_workspace_bytes(int dtype, int mode, int64_t N, int64_t K, int64_t K2);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
-// ---- gemm_split.hip: float32 PLAIN / CONCAT / grouped (groups > 0) ----
+// ---- gemm_split.hip: float32 PLAIN / CONCAT / GRU / grouped (groups > 0) ----
 // whether a product takes the split path (K: both operands' columns).  Up to
 // 32 columns and 256 k the float32 instruction keeps up with memory and needs
 // fewer registers (10^6 x 64 x 16: 60 us against 69; x 602 x 8: 557 against 510)
 bool gemm_splits(int dtype, int mode, int64_t N, int64_t K);
-size_t split_workspace_bytes(int64_t N, int64_t K, int64_t K2, int groups);
+size_t split_workspace_bytes(int mode, int64_t N, int64_t K, int64_t K2, int groups);
 hipError_t launch_gemm_split(const GemmArgs& g, hipStream_t st);
 // grouped GEMM over row ranges of whole kRelTile-row tiles (mode ignored;
 // M = row capacity, a multiple of kRelTile)
@@ -192,9 +201,5 @@ struct RelLayout {
 bool rel_layout(int32_t num_src, int64_t num_edges, int32_t num_rel, RelLayout* L);
 hipError_t launch_rel_build(const saga_plan& p, const saga_rel_plan& rel, const RelLayout& L,
                             hipStream_t st);
-
-// ---- layer helpers (gather.hip) ----
-hipError_t launch_fold_attention(const float* w, int64_t K, int64_t F, int heads, const float* al,
-                                 const float* ar, float* w_ext, int64_t ld_ext, hipStream_t st);
 
 }  // namespace saga

@@ -107,3 +107,72 @@ def test_infinities_and_nan():
     assert np.array_equal(got[inf], ref[inf])
     fin = np.isfinite(ref)
     assert np.allclose(got[fin], ref[fin], rtol=1e-5, atol=1e-4)
+
+
+def _sig(x):
+    return 1 / (1 + np.exp(-x))
+
+
+@pytest.mark.parametrize("M,K,F,special", [(1, 1, 16, False), (65, 33, 32, False), (130, 70, 48, False),
+                                           (200, 64, 64, False), (64, 5, 64, True)])
+def test_gru(M, K, F, special):
+    """Both products share the r and z accumulators; |h| < 1 after the gates,
+    whose slopes are at most 1, so the products' bound carries over."""
+    rng = np.random.default_rng(M + K + F)
+    a = rng.standard_normal((M, K), dtype=np.float32)
+    h = rng.standard_normal((M, F), dtype=np.float32)
+    w, w2 = (rng.uniform(-0.3, 0.3, (k, 3 * F)).astype(np.float32) for k in (K, F))
+    b, b2 = (rng.uniform(-1, 1, 3 * F).astype(np.float32) for _ in range(2))
+    if special:  # a row past the split's range
+        a[5] *= np.float32(1e20)
+    op = S.saga_gemm_op()
+    op.mode = S.SAGA_GEMM_GRU
+    t = [torch.from_numpy(x).to(DEV) for x in (w, w2, b, b2)]
+    am, hm = _mat(a), _mat(h)
+    out = S.padded_empty(M, F, torch.float32, DEV)
+    ws = S.workspace(S.saga_apply_vertex_workspace_size(op, K, F, 3 * F), DEV)
+    S.saga_apply_vertex(op, S.cmat(am), S.cmat(t[0]), S.cmat(hm), S.cmat(t[1]), S._ptr(t[2]), S._ptr(t[3]),
+                        S.mat(out), S._ptr(ws), ws.numel(), S.stream_handle())
+    gi, gh = a.astype(np.float64) @ w + b, h.astype(np.float64) @ w2 + b2
+    with np.errstate(over="ignore"):
+        r, z = _sig(gi[:, :F] + gh[:, :F]), _sig(gi[:, F:2 * F] + gh[:, F:2 * F])
+        n = np.tanh(gi[:, 2 * F:] + r * gh[:, 2 * F:])
+    ref = (1 - z) * n + z * h
+    err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
+    if special:
+        err = err[np.abs(gi).max(1) < 1e6]
+    assert err.max() <= 2e-5
+
+
+@pytest.mark.parametrize("Fi,heads,D,mean", [(3, 1, 4, False), (33, 2, 4, True), (100, 8, 16, False), (64, 8, 8, True)])
+def test_attention_vectors_folded_into_the_weights(Fi, heads, D, mean):
+    """GAT layer against the oracle: z, el and er come from one product."""
+    from gpu_util import dev_padded, graph
+    from synth import graphs as G
+
+    V = 300
+    rng = np.random.default_rng(Fi)
+    src, dst = rng.integers(0, V, 1500), rng.integers(0, V, 1500)
+    rp, col = G.to_in_csr(V, src, dst)
+    F = heads * D
+    x = rng.standard_normal((V, Fi), dtype=np.float32)
+    w = rng.uniform(-0.5, 0.5, (Fi, F)).astype(np.float32)
+    al, ar = (rng.uniform(-1, 1, (heads, D)).astype(np.float32) for _ in range(2))
+    b = rng.uniform(-1, 1, D if mean else F).astype(np.float32)
+    from paper_2009_00804_amd import layers as LY
+    g = graph(rp, col)
+    layer = LY.Layer(g, "gat", Fi, D if mean else F, {"w": w, "b": b, "attn_l": al, "attn_r": ar}, heads=heads,
+                     head_mean=mean, act="none")
+    got = layer(dev_padded(x)).cpu().numpy().astype(np.float64)
+    z = (x.astype(np.float64) @ w).reshape(V, heads, D)
+    el, er = (z * al).sum(2), (z * ar).sum(2)
+    ref = np.zeros((V, heads, D))
+    for v in range(V):
+        u = col[rp[v]:rp[v + 1]]
+        if u.size:
+            s = el[u] + er[v]
+            s = np.where(s > 0, s, 0.2 * s)
+            p = np.exp(s - s.max(0))
+            ref[v] = (p[:, :, None] * z[u]).sum(0) / p.sum(0)[:, None]
+    ref = (ref.mean(1) if mean else ref.reshape(V, F)) + b
+    assert np.abs(got - ref).max() <= 1e-4 * max(1.0, np.sqrt((ref ** 2).mean()))
