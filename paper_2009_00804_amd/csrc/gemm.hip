@@ -595,10 +595,7 @@ Tiling choose(int dtype, int mode, int64_t N, int64_t K) {
   // registers two more A slots would hold buy occupancy instead; measured
   // on the 2^21 x 128 x 41 bfloat16 transform: 0.175 -> 0.162 ms)
   if (nt <= 5) return Tiling{(int)nt, chunks(dtype, K) <= 4 ? 2 : 4};
-  // 128-column tiles (bfloat16; more columns: several tiles along N), eight
-  // waves of 16 rows, measured best on the 2^21 x 602 x 128 transform and on
-  // 131072 x 512 x 256
-  return Tiling{8, 4};
+  return Tiling{8, 4};  // 128-column tiles; also the weight-resident kernel's packed rows
 }
 
 int kc_of(int dtype) { return dtype == SAGA_BF16 ? Mma<uint16_t>::KC : Mma<float>::KC; }
@@ -652,29 +649,21 @@ hipError_t launch_bres(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The weight-resident kernel takes bfloat16 PLAIN products with 80 < N <=
-// 128 (narrower outputs use the narrow tiles) and 192 <= K <= 608.  On
-// 2^21 rows x 128 columns against the streamed tiles: 0.32 / 0.35 ms at
-// K = 192 (one 16-row tile per wave), 0.37 / 0.42 ms at K = 256, 0.49 /
-// 0.55 at 384 and 0.69 / 0.80 at 602 (two tiles per wave, three A slots:
-// as fast as four, which spill registers); at K = 128 the streamed tiles
-// are as fast.
-hipError_t maybe_bres(const GemmArgs& g, hipStream_t st, bool* used) {
-  *used = false;
-  if (g.dtype != SAGA_BF16 || g.mode != SAGA_GEMM_PLAIN || g.N > 128 || g.K > 32 * kResHalfChunks)
-    return hipSuccess;
-  if (g.N <= 80 || g.K < 192) return hipSuccess;
-  *used = true;
-  return g.K < 256 ? launch_bres<1, 8, 4>(g, st) : launch_bres<2, 8, 3>(g, st);
+// The weight-resident kernel takes bfloat16 PLAIN products with 80 < N <= 128
+// (narrower outputs use the narrow tiles) and 256 <= K <= 608.  On 2^21 rows x
+// 128 columns against streamed weights (gemm_stream.hip): 0.353 / 0.362 ms at
+// K = 256, 0.454 / 0.477 at 384, 0.663 / 0.679 at 602 (two 16-row tiles per
+// wave, three A slots: as fast as four, which spill registers); below K = 256
+// the streamed weights win (K = 192: 0.333 / 0.320).
+bool takes_bres(int dtype, int mode, int64_t N, int64_t K) {
+  return dtype == SAGA_BF16 && mode == SAGA_GEMM_PLAIN && N > 80 && N <= 128 && K >= 256 &&
+         K <= 32 * kResHalfChunks;
 }
 
 template <typename T>
 hipError_t dispatch(const GemmArgs& g, hipStream_t st) {
-  if constexpr (sizeof(T) == 2) {
-    bool used = false;
-    const hipError_t e = maybe_bres(g, st, &used);
-    if (used || e != hipSuccess) return e;
-  }
+  if constexpr (sizeof(T) == 2)
+    if (takes_bres(g.dtype, g.mode, g.N, g.K)) return launch_bres<2, 8, 3>(g, st);
   const Tiling t = choose(g.dtype, g.mode, g.N, g.mode == SAGA_GEMM_CONCAT ? g.K + g.K2 : g.K);
   if constexpr (sizeof(T) == 2) {  // float32: gemm_split.hip
     if (g.mode == SAGA_GEMM_GRU) {
@@ -765,14 +754,26 @@ void grouped_packed(int dtype, int64_t N, int64_t K, int64_t* np, int64_t* kp) {
 
 }  // namespace
 
+// One k chunk an operand (K, K2 <= 64) and a concat or more than 208 columns:
+// the 128-column tiles, whose single step prefetches nothing, stay (578959 x
+// (31 + 31) x 250: 202 us, streamed 230; 575339 x (64 + 64) x 98: 91, 97; but
+// 300000 x 20 x 160: 59, 37).
+bool gemm_streams(int dtype, int mode, int64_t N, int64_t K, int64_t K2) {
+  if (dtype != SAGA_BF16 || mode == SAGA_GEMM_GRU || N <= 80 || takes_bres(dtype, mode, N, K)) return false;
+  return K > 64 || K2 > 64 || (mode == SAGA_GEMM_PLAIN && N <= 208);
+}
+
 size_t gemm_workspace_bytes(int dtype, int mode, int64_t N, int64_t K, int64_t K2) {
   if (mode != SAGA_GEMM_CONCAT && mode != SAGA_GEMM_GRU) K2 = 0;
+  if (gemm_streams(dtype, mode, N, K, K2)) return stream_workspace_bytes(N, K, K2);
   if (gemm_splits(dtype, mode, N, K + K2)) return split_workspace_bytes(mode, N, K, K2, 1);
   return packed_layout(dtype, mode, N, K, K2).bytes;
 }
 
 hipError_t launch_gemm(const GemmArgs& g0, hipStream_t st) {
   if (g0.M == 0) return hipSuccess;
+  if (gemm_streams(g0.dtype, g0.mode, g0.N, g0.K, g0.mode == SAGA_GEMM_PLAIN ? 0 : g0.K2))
+    return launch_gemm_stream(g0, st);
   if (g0.forms() || gemm_splits(g0.dtype, g0.mode, g0.N, g0.K + (g0.mode == SAGA_GEMM_CONCAT ? g0.K2 : 0)))
     return launch_gemm_split(g0, st);
   const Packed pk = packed_layout(g0.dtype, g0.mode, g0.N, g0.K, g0.K2);

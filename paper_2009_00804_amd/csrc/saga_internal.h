@@ -184,6 +184,11 @@ hipError_t launch_gemm_split(const GemmArgs& g, hipStream_t st);
 size_t gemm_grouped_workspace_bytes(int dtype, int groups, int64_t N, int64_t K);
 hipError_t launch_gemm_grouped(const GemmArgs& g, hipStream_t st);
 
+// ---- gemm_stream.hip: bfloat16 PLAIN / CONCAT with more than 80 columns ----
+bool gemm_streams(int dtype, int mode, int64_t N, int64_t K, int64_t K2);
+size_t stream_workspace_bytes(int64_t N, int64_t K, int64_t K2);
+hipError_t launch_gemm_stream(const GemmArgs& g, hipStream_t st);
+
 // ---- rel.hip ----
 constexpr int kRelTile = SAGA_REL_TILE;  // rows per grouped-GEMM tile
 constexpr int kRelMaxRelations = SAGA_REL_MAX_RELATIONS;

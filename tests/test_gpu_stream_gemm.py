@@ -1,0 +1,49 @@
+"""bfloat16 products with more than 80 columns: edges of the column blocks (one
+block up to 13 column tiles, blocks of at most ten past that, of seven over few rows), k chunks of 64, row
+tiles, both operands of the concat form, the split output.
+
+Reference: float64 of the bfloat16 inputs.  Bound: products exact in float32,
+sums of K terms (K 2^-24 of the magnitudes), one rounding to bfloat16."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev_padded, to_np
+from paper_2009_00804_amd import saga as S
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _bf(x):
+    return torch.from_numpy(x).to(torch.bfloat16).to(torch.float64).numpy()
+
+
+@pytest.mark.parametrize("M,K,K2,N,split", [
+    (1, 1, 0, 81, 0), (63, 63, 0, 96, 0), (64, 64, 0, 112, 64), (65, 65, 0, 128, 0), (200, 128, 0, 129, 0),
+    (130, 129, 0, 200, 128), (70, 191, 0, 256, 0), (33, 40, 0, 257, 0), (50, 100, 0, 300, 0),
+    (131071, 24, 0, 208, 0), (131072, 72, 0, 209, 0), (65536, 449, 0, 100, 64), (40001, 33, 0, 260, 0),
+    (400001, 16, 0, 88, 0), (32767, 72, 0, 200, 0), (32768, 72, 0, 200, 0), (65537, 16, 448, 90, 0),
+    (100, 64, 1, 90, 0), (129, 1, 65, 144, 0), (300, 300, 300, 200, 0), (33000, 130, 40, 170, 0),
+    (77, 700, 0, 128, 0), (31, 8, 8, 1000, 0)])
+def test_products(M, K, K2, N, split):
+    rng = np.random.default_rng(M + K + K2 + N)
+    a = [rng.standard_normal((M, k), dtype=np.float32) for k in (K, K2) if k]
+    w = [rng.uniform(-1, 1, (k, N)).astype(np.float32) for k in (K, K2) if k]
+    b = rng.uniform(-1, 1, N).astype(np.float32)
+    op = S.saga_gemm_op()
+    op.dtype, op.mode = S.SAGA_BF16, S.SAGA_GEMM_CONCAT if K2 else S.SAGA_GEMM_PLAIN
+    out = S.padded_empty(M, split or N, torch.bfloat16, DEV)
+    tail = S.padded_empty(M, N - split, torch.bfloat16, DEV) if split else None
+    if split:
+        op.split_col, op.tail = split, S.mat(tail)
+    ad = [dev_padded(x, torch.bfloat16) for x in a] + [None]
+    wd = [torch.from_numpy(x).to(DEV).to(torch.bfloat16) for x in w] + [None]
+    bd = torch.from_numpy(b).to(DEV)
+    ws = S.workspace(S.saga_apply_vertex_workspace_size(op, K, K2, N), DEV)
+    S.saga_apply_vertex(op, S.cmat(ad[0]), S.cmat(wd[0]), S.cmat(ad[1]), S.cmat(wd[1]), S._ptr(bd), None,
+                        S.mat(out), S._ptr(ws), ws.numel(), S.stream_handle())
+    got = np.concatenate([to_np(out), to_np(tail)], 1) if split else to_np(out)
+    ref = sum(_bf(x) @ _bf(y) for x, y in zip(a, w)) + b
+    mag = sum(np.abs(_bf(x)) @ np.abs(_bf(y)) for x, y in zip(a, w)) + np.abs(b)
+    assert np.all(np.abs(got - ref) <= (K + K2 + 2) * 2.0 ** -24 * mag + 2.0 ** -8 * np.abs(ref) + 1e-30)
