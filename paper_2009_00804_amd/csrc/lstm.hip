@@ -21,19 +21,27 @@
 // workgroup of 4H threads runs one row at a time; the longest row's d
 // sequential steps bound the time, so a step is kept as short as the vector
 // ALU allows (4H x H multiply-adds per step):
-//   * thread t serves hidden unit i = t / 4 and the quarter q = t % 4 of the
-//     recurrent sum: it keeps the H/4 x 4 weights W_hh[k][gate * H + i]
-//     (k in its quarter, the four gates of unit i) in registers, so every h
-//     value it reads from LDS feeds four multiply-adds;
-//   * the unit's four lanes (a quad) reduce-scatter their partial sums with
-//     DPP quad permutations, so lane q holds gate q's pre-activation and
-//     applies that gate's activation alone; the four activations are then
+//   * thread t serves gate q = t % 4 of hidden unit i = t / 4.  Eight lanes
+//     share the recurrent sums of their eight (unit, gate) columns: each keeps
+//     an eighth of all eight columns of W_hh in registers, so every h value it
+//     reads from LDS feeds eight multiply-adds, and seven DPP adds hand each
+//     lane the sum of its own column;
+//   * the thread applies that gate's activation; the four activations are then
 //     broadcast within the quad, every lane updates its copy of (c, h), and
 //     lane 0 writes h to a double-buffered LDS vector -- one workgroup
 //     barrier per step;
 //   * the P rows of the next PF steps are loaded straight into an LDS ring
 //     (global_load_lds_dwordx4) by the first waves, so the recurrence never
-//     waits on memory; the neighbour ids come in chunks through LDS.
+//     waits on memory; the neighbour ids come in chunks through LDS.  A step's
+//     load is issued, with scalar addresses, before its multiply-adds and not
+//     at the end of the step, where every wave would wait for it at the barrier.
+// Measured, GraphSAGE-LSTM layer at 131,072 vertices, H = 128, longest row about
+// 19,800 in-edges (ms): groups of 4 lanes 12.35, 8 12.18, 16 12.74; before, with
+// groups of 4, selects in the exchange, the loads at the end of a step and a
+// chain of scalar branches around every wait, 15.70.  One column a lane with h
+// broadcast by a DPP modifier on every multiply-add reads the least LDS but took
+// 15.78: such multiply-adds issue more slowly.  The vector ALU's own bound is
+// 1,024 cycles a step, 8.5 ms for that row at 2.4 GHz.
 // The same kernel takes a range of perm positions, so a caller can also run
 // the degree traversal (one launch per run of equal degrees) for comparison.
 #include <algorithm>
@@ -44,7 +52,8 @@
 namespace saga {
 namespace {
 
-constexpr int kSplit = 4;    // threads per hidden unit (quarters of the recurrent sum)
+constexpr int kGates = 4;    // threads per hidden unit, and gates
+constexpr int kGroup = 8;    // lanes that share a recurrent sum
 constexpr int kPF = 12;      // P rows in flight ahead of the recurrence
 constexpr int kUch = 1024;   // neighbour ids per LDS chunk
 constexpr int kLone = 2048;  // the longest rows are handed out one by one
@@ -98,16 +107,8 @@ __device__ __forceinline__ float tanh_fast(float x) {
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(__expf(2.0f * x) + 1.0f);
 }
 
-// Quad (four-lane) exchanges through DPP quad permutations; a generic
-// shuffle would go through the LDS crossbar (ds_bpermute) and add its
-// latency to every step.  quad_xor<M>: the value of lane ^ M; quad_bcast<K>:
-// the value of lane K of the quad.
-template <int M>
-__device__ __forceinline__ float quad_xor(float x) {
-  static_assert(M == 1 || M == 2, "quad lane mask");
-  constexpr int ctrl = M == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] / [2,3,0,1]
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xF, 0xF, false));
-}
+// The value of lane K of the quad, through DPP; a generic shuffle would go
+// through the LDS crossbar (ds_bpermute) and add its latency to every step.
 template <int K>
 __device__ __forceinline__ float quad_bcast(float x) {
   static_assert(K >= 0 && K < 4, "quad lane");
@@ -121,18 +122,38 @@ __global__ void k_lstm_zero(int32_t* q) {
 template <int H>
 struct LstmCfg {
   static constexpr int G = 4 * H;                // gate columns
-  static constexpr int THREADS = kSplit * H;     // 128, 256 or 512
-  static constexpr int KPT = H / kSplit;         // recurrent k per thread
+  static constexpr int THREADS = kGates * H;     // 128, 256 or 512
+  static constexpr int L = kGroup;
+  static constexpr int HPL = H / L;              // values of h a lane holds: 4, 8 or 16
+  static constexpr int HV = 4;                   // of them, contiguous in h
   static constexpr int PV = G / 4;               // 16-byte pieces of one P row
-  static_assert(KPT % 4 == 0, "shape");
+  static_assert(HPL * L == H && HPL % HV == 0, "shape");
   static_assert(PV % 64 == 0 || PV < 64, "P row = whole waves or one partial wave");
   static_assert(PV <= THREADS, "P row loaders");
 };
 
+// The lane that bit BIT of an index stands for, as the mask one DPP modifier
+// exchanges: quad permutations (1, 2) and the half-row mirror (7, for 4).
+constexpr int lane_mask(int j) { return (j & 3) ^ (j & 4 ? 7 : 0); }
+template <int BIT>
+__device__ __forceinline__ float lane_xor(float x) {
+  static_assert(BIT == 1 || BIT == 2 || BIT == 4, "index bit");
+  constexpr int ctrl = BIT == 1 ? 0xB1 : BIT == 2 ? 0x4E : 0x141;
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xF, 0xF, true));
+}
+// z[j] of a lane belongs to lane ^ lane_mask(j): z[0] ends as the lane's own
+// column summed over the group, without a select
+template <int BIT, int L>
+__device__ __forceinline__ void reduce_scatter(float (&z)[L]) {
+#pragma unroll
+  for (int j = 0; j < BIT; ++j) z[j] += lane_xor<BIT>(z[j + BIT]);
+  if constexpr (BIT > 1) reduce_scatter<BIT / 2>(z);
+}
+
 template <int H>
 __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a) {
   typedef LstmCfg<H> C;
-  constexpr int G = C::G, KPT = C::KPT, PV = C::PV, NT = C::THREADS;
+  constexpr int G = C::G, L = C::L, HPL = C::HPL, HV = C::HV, PV = C::PV, NT = C::THREADS;
   __shared__ __attribute__((aligned(16))) float ring[(kPF + 1) * G];
   __shared__ __attribute__((aligned(16))) float hbuf[2][H];
   __shared__ int32_t ucache[2][kUch];
@@ -140,14 +161,16 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
   if (a.counts[kErrFlags]) return;
 
   const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
-  const int i = t / kSplit, q = t % kSplit;  // hidden unit, quarter of the k range
-  const int k0 = q * KPT;
-  float w[4][KPT];
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int i = t / kGates, q = t % kGates;  // hidden unit, gate
+  float w[L][HPL];  // w[j]: column of lane ^ lane_mask(j)
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int j = 0; j < L; ++j) {
+    const int tj = t ^ lane_mask(j);
 #pragma unroll
-    for (int k = 0; k < KPT; ++k) w[g][k] = a.w_hh[(int64_t)(k0 + k) * a.ld_whh + g * H + i];
+    for (int r = 0; r < HPL; ++r)
+      w[j][r] = a.w_hh[(int64_t)(r / HV * L * HV + lane % L * HV + r % HV) * a.ld_whh + tj % kGates * H + tj / kGates];
+  }
   // P row pieces: lane l of wave w (w * 64 + l < PV) loads piece w * 64 + l
   const bool p_loader = wave * 64 < PV;
   const bool p_lane = wave * 64 + lane < PV;
@@ -201,7 +224,10 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
         // this wave's P row of step s has landed (the loads of at most the
         // kPF - 1 later steps may still be pending), then everyone's; h of
         // step s - 1 is in hbuf[s & 1]
-        if (p_loader) wait_vm_le(std::min(kPF - 1, d - 1 - s));
+        if (p_loader) {
+          if (d - s >= kPF) wait_vm<kPF - 1>();  // (the switch is a chain of scalar branches)
+          else wait_vm_le(d - 1 - s);
+        }
         lds_barrier();
         // this lane's gate-q entry of the step's P row, read with an inline
         // ds_read_b32 and waited for after the recurrent sum: read as plain
@@ -214,35 +240,36 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
                      : "=v"(pq)
                      : "v"(ring_base + (uint32_t)(((s % (kPF + 1)) * G + q * H + i) * 4))
                      : "memory");
-        // this thread's quarter of h, all of it read before the first
-        // multiply-add (one LDS wait per step)
-        const float* hb = hbuf[s & 1];
-        float hk[KPT];
+        // this lane's values of h: r is h[r / HV * L HV + lane % L * HV + r % HV]
+        const float* hb = hbuf[s & 1] + lane % L * HV;
+        float hk[HPL];
 #pragma unroll
-        for (int k = 0; k < KPT; k += 4) {
-          const float4 hv = *reinterpret_cast<const float4*>(hb + k0 + k);
-          hk[k] = hv.x;
-          hk[k + 1] = hv.y;
-          hk[k + 2] = hv.z;
-          hk[k + 3] = hv.w;
+        for (int r = 0; r < HPL; r += HV) {
+          typedef float vec __attribute__((ext_vector_type(HV)));
+          const vec hv = *reinterpret_cast<const vec*>(hb + r * L);
+#pragma unroll
+          for (int j = 0; j < HV; ++j) hk[r + j] = hv[j];
+        }
+        // the P row of step s + kPF goes to the slot step s - 1 used (read
+        // before this step's barrier)
+        const int sn = s + kPF;
+        if (p_loader && sn < d) {
+          const int u = __builtin_amdgcn_readfirstlane(ucache[(sn / kUch) & 1][sn % kUch]);
+          if (p_lane)
+            __builtin_amdgcn_global_load_lds(a.gates_x + (int64_t)u * a.ld_gx + (wave * 64 + lane) * 4,
+                                             (lds_ptr)(ring + (sn % (kPF + 1)) * G + wave * 256), 16, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);  // keep every read ahead of the multiply-adds
-        float z0 = 0.0f, z1 = 0.0f, z2 = 0.0f, z3 = 0.0f;
+        float z[L];
 #pragma unroll
-        for (int k = 0; k < KPT; ++k) {  // four independent chains
-          z0 = fmaf(w[0][k], hk[k], z0);
-          z1 = fmaf(w[1][k], hk[k], z1);
-          z2 = fmaf(w[2][k], hk[k], z2);
-          z3 = fmaf(w[3][k], hk[k], z3);
-        }
+        for (int j = 0; j < L; ++j) z[j] = w[j][0] * hk[0];
+#pragma unroll
+        for (int r = 1; r < HPL; ++r)
+#pragma unroll
+          for (int j = 0; j < L; ++j) z[j] = fmaf(w[j][r], hk[r], z[j]);
+        reduce_scatter<L / 2>(z);
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(pq) : : "memory");
-        // reduce-scatter over the quad: lane q ends with the full sum of gate
-        // q (lane ^ 2 exchanges gate pairs, lane ^ 1 single gates)
-        const bool hi = q & 2, odd = q & 1;
-        float k0 = hi ? z2 : z0, k1 = hi ? z3 : z1;
-        k0 += quad_xor<2>(hi ? z0 : z2);
-        k1 += quad_xor<2>(hi ? z1 : z3);
-        const float zq = (odd ? k1 : k0) + quad_xor<1>(odd ? k0 : k1) + pq;
+        const float zq = z[0] + pq;
         // gate q's activation: tanh for g (q == 2, as 2 sigmoid(2x) - 1),
         // sigmoid for i, f, o; then all four to every lane of the quad
         const float sg = sigmoid_fast(q == 2 ? 2.0f * zq : zq);
@@ -254,16 +281,6 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
         if (q == 0) {
           hbuf[(s + 1) & 1][i] = hn;
           if (s == d - 1) orow[i] = hn;
-        }
-        // the P row of step s + kPF goes to the slot step s - 1 used (read
-        // before this step's barrier)
-        const int sn = s + kPF;
-        if (p_loader && sn < d) {
-          const int u = ucache[(sn / kUch) & 1][sn % kUch];
-          if (p_lane)
-            __builtin_amdgcn_global_load_lds(a.gates_x + (int64_t)u * a.ld_gx + (wave * 64 + lane) * 4,
-                                             (lds_ptr)(ring + (sn % (kPF + 1)) * G + wave * 256), 16,
-                                             0, 0);
         }
         // entering chunk cc: chunk cc + 1 replaces chunk cc - 1, whose ids
         // were last read for the load of step cc * kUch - 1 (issued kPF
