@@ -1,5 +1,7 @@
 // ApplyVertex in float32: PLAIN, CONCAT, GRU and grouped products on the bfloat16
 // matrix cores, every float32 operand as an exact sum of three bfloat16 values.
+#include <type_traits>
+
 #include "gemm_device.h"
 
 namespace saga {
@@ -9,16 +11,24 @@ namespace {
 // float32 products on the bfloat16 matrix cores.  Every float32 value is the
 // exact sum of three bfloat16 values, x = x1 + x2 + x3 (round to nearest, then
 // the remainders: 8 + 8 + 8 bits of significand), so
-//   a w = a1 w1 + (a1 w2 + a2 w1) + (a1 w3 + a2 w2 + a3 w1) + O(2^-26 |a w|)
-// and the six products, each exact in float32, are accumulated in float32 by
-// v_mfma_f32_16x16x32_bf16.  One such instruction takes 32 k at 16 times the
-// rate of v_mfma_f32_16x16x4f32, so six of them take 3/8 of its time, and an
-// accumulator is rounded six times per 32 k instead of eight.  Measured on
-// 2^21 x 602 x 128: 2.92 -> 1.87 ms, relative error against float64 4.0e-7 ->
-// 3.4e-7; every size tried came out nearer to float64 than the float32
-// instruction.  What bounds it: the matrix cores run at half their rate at the
-// 1.87 GHz the power limit leaves under this load (the products alone take
-// 1.15 ms, the A loads add 0.35, the weights 0.27, the stores 0.14).
+//   a w = a1 w1 + (a1 w2 + a2 w1) + (a1 w3 + a2 w2 + a3 w1) + rest
+// with |rest| <= 2^-24.2 |a w|, 2^-27.5 |a w| in the root mean square, and the
+// six products are accumulated in float32 by v_mfma_f32_16x16x32_bf16.  One such
+// instruction takes 32 k at 16 times the rate of v_mfma_f32_16x16x4f32, so six of
+// them take 3/8 of its time.
+//
+// Accumulation.  The instruction adds its 32 products to the accumulator eight
+// at a time and rounds after each eight, v_mfma_f32_16x16x4f32 after each
+// product.  a1 w1 has accumulators of its own, the five small terms (2^-8 of it)
+// others, added at the end: the large accumulator is then rounded at most once
+// per eight k, and not at all where a and w are zero, so that no input has more
+// roundings of its full magnitude than with the float32 instruction.  (All six in
+// one accumulator are six roundings a chunk: nearer to float64 than the float32
+// instruction on dense rows, but up to 2.1 times further off on rows with one to
+// three nonzeros per 32 k.)  Relative error against float64, float32 instruction /
+// one accumulator / two, 8192 rows x 128: K = 602 normal 4.4e-7 / 3.7e-7 / 1.3e-7,
+// after ReLU 3.1e-7 / 3.5e-7 / 1.0e-7, 2 % of values nonzero 6.7e-8 / 1.3e-7 /
+// 3.0e-8.
 //
 // The split needs its operands' magnitudes well inside the float32 range: a
 // row of A (or a column of W) whose largest magnitude is 2^60 or more
@@ -94,7 +104,10 @@ __host__ __device__ inline WSrc wsrc2(const GemmArgs& g) {
 // the compiler would otherwise wait for every one in flight before any LDS
 // read.  Loads return in order, so the explicit wait at the top of a step, at
 // most the newest A loads pending, covers the older weight loads.
-template <int MT, int NT, int NW>
+//
+// CONCAT: the chunks of both operands make one stream, the second operand's from
+// chunk n1 on, and their images lie one after another.
+template <int MT, int NT, int NW, bool CONCAT = false>
 struct Split3 {
   typedef float T;
   static constexpr int THREADS = 64 * NW;
@@ -105,21 +118,39 @@ struct Split3 {
   static constexpr int LB = (STAGE + THREADS - 1) / THREADS;
   static constexpr int KC = 32;
 
+  // rows of one operand
+  struct Rows {
+    const float* a;
+    int64_t lda, K;
+    const int32_t* arow;
+    __device__ int chunks() const { return (int)((K + KC - 1) / KC); }
+  };
   struct Ctx {
     const float* row[MT];  // this lane's A rows
-    int64_t K;
+    int k0, kmax;          // their operand's first chunk; first column of a row's last 16-byte piece
     const uint4* Wi;       // this column block's image: chunk c at c * STAGE
     lds_uint4* ring;
-    int last, kmax;        // last chunk; first column of a row's last 16-byte piece
+    int last, n1;          // last chunk; the second operand's first
+    Rows op2;              // CONCAT
+    int64_t M, row0;
   };
+  __device__ __forceinline__ static void set_rows(Ctx& c, const Rows& o, int first) {
+    int64_t off[MT];
+    row_offsets(o.arow, o.lda, c.M, c.row0, off);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) c.row[mt] = o.a + off[mt];
+    c.k0 = first;
+    c.kmax = (int)((o.K - 1) / 4 * 4);
+  }
 
   // A values of chunk c: columns 32 c + 4 (lane / 16) .. + 3 and the same 16
   // further on (a load instruction then covers 64 contiguous bytes of every
   // row; k_pack_split orders its k alike).  A piece that starts at or past K
   // reads the row's last piece instead (masked when split).
-  __device__ __forceinline__ static void load_a(const Ctx& c, int chunk, uint4 (&a)[MT][2]) {
+  __device__ __forceinline__ static void load_a(Ctx& c, int chunk, uint4 (&a)[MT][2]) {
+    if (CONCAT && chunk == c.n1) set_rows(c, c.op2, c.n1);
     const int lg = (threadIdx.x & 63) >> 4;
-    const int k = chunk * KC + lg * 4;
+    const int k = (chunk - c.k0) * KC + lg * 4;
     const int k0 = min(k, c.kmax), k1 = min(k + 16, c.kmax);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -127,11 +158,12 @@ struct Split3 {
       a[mt][1] = *reinterpret_cast<const uint4*>(c.row[mt] + k1);
     }
   }
-  __device__ __forceinline__ static void mask(const Ctx& c, int chunk, uint4 (&a)[MT][2]) {
+  // zeros past column K, for the chunk-th chunk of an operand
+  __device__ __forceinline__ static void mask(int64_t K, int chunk, uint4 (&a)[MT][2]) {
     const int lg = (threadIdx.x & 63) >> 4;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int64_t left = c.K - (chunk * KC + lg * 4 + h * 16);
+      const int64_t left = K - (chunk * KC + lg * 4 + h * 16);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         if (left < 4) a[mt][h].w = 0;
@@ -193,8 +225,8 @@ struct Split3 {
   }
   // Column tile g goes to accumulator g, or g + SHIFT from tile FROM on.
   template <int U, bool LOAD, bool MASK, bool LAST, int FROM, int SHIFT, int NA>
-  __device__ __forceinline__ static void step(const Ctx& c, int i, uint4 (&a)[2][MT][2], Parts (&ap)[2],
-                                              float (&amax)[MT], f32x4 (&acc)[MT][NA]) {
+  __device__ __forceinline__ static void step(Ctx& c, int i, const Rows& op1, uint4 (&a)[2][MT][2], Parts (&ap)[2],
+                                              float (&amax)[MT], f32x4 (&acc)[MT][NA], f32x4 (&lo)[MT][NA]) {
     // chunk i's weights landed (only chunk i + 1's A loads are newer), for
     // every wave; the other stage is free again
     wait_vm<LAST ? 0 : 2 * MT>();
@@ -205,20 +237,24 @@ struct Split3 {
     if constexpr (!LAST) issue_b(c, i + 1, U ^ 1);
     if constexpr (LOAD) load_a(c, i + 2, a[U]);
     __builtin_amdgcn_sched_barrier(0);
-    // smallest products first
+    // smallest products first; all but the last into `lo`
     constexpr int QA[6] = {2, 1, 0, 1, 0, 0}, QB[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
     for (int g = 0; g < NT; ++g) {
       if (g + 1 < NT) read_b(Bs, g + 1, b[(g + 1) & 1]);
       if constexpr (MASK) {
-        if (g == G0) mask(c, i + 1, a[U ^ 1]);
+        if (g == G0) mask(CONCAT ? c.op2.K : op1.K, i + 1 - (CONCAT ? c.n1 : 0), a[U ^ 1]);
+      }
+      if constexpr (CONCAT && !LAST) {
+        if (g == G0 && i + 2 == c.n1) mask(op1.K, i + 1, a[U ^ 1]);
       }
 #pragma unroll
       for (int q = 0; q < 6; ++q) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[mt][g + (g >= FROM ? SHIFT : 0)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              part(ap[U], mt, QA[q]), b[g & 1][QB[q]], acc[mt][g + (g >= FROM ? SHIFT : 0)], 0, 0, 0);
+        for (int mt = 0; mt < MT; ++mt) {
+          f32x4& d = (q == 5 ? acc : lo)[mt][g + (g >= FROM ? SHIFT : 0)];
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part(ap[U], mt, QA[q]), b[g & 1][QB[q]], d, 0, 0, 0);
+        }
         if (!LAST && g >= G0) {
           const int slot = (g - G0) * 6 + q;
 #pragma unroll
@@ -229,51 +265,67 @@ struct Split3 {
       }
     }
   }
-  // acc += A[tile0 .. tile0 + BM) x the column block's image; amax: this
-  // lane's part of its rows' largest magnitudes
-  template <int FROM = NT, int SHIFT = 0, int NA = NT>
-  __device__ __forceinline__ static void phase(const float* __restrict__ A, int64_t lda, int64_t M,
-                                               int64_t K, const uint4* __restrict__ Wi,
-                                               int64_t tile0, uint4* ring, float (&amax)[MT],
-                                               f32x4 (&acc)[MT][NA],
-                                               const int32_t* __restrict__ arow = nullptr) {
+  // acc, lo += A[tile0 .. tile0 + BM) x the column block's image; amax: this
+  // lane's part of its rows' largest magnitudes.  CH > 0: the number of chunks.
+  template <int FROM = NT, int SHIFT = 0, int CH = 0, int NA = NT>
+  __device__ __forceinline__ static void phase(const Rows& op1, const Rows& op2, int64_t M,
+                                               const uint4* __restrict__ Wi, int64_t tile0, uint4* ring,
+                                               float (&amax)[MT], f32x4 (&acc)[MT][NA], f32x4 (&lo)[MT][NA]) {
     Ctx c;
-    int64_t off[MT];
-    row_offsets(arow, lda, M, tile0 + (threadIdx.x >> 6) * MT * 16, off);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) c.row[mt] = A + off[mt];
-    c.K = K;
+    c.M = M;
+    c.row0 = tile0 + (threadIdx.x >> 6) * MT * 16;
+    set_rows(c, op1, 0);
+    c.n1 = op1.chunks();
+    c.op2 = op2;
     c.Wi = Wi;
     c.ring = (lds_uint4*)ring;
-    c.last = (int)((K + KC - 1) / KC) - 1;
-    c.kmax = (int)((K - 1) / 4 * 4);
+    c.last = (CH > 0 ? CH : CONCAT ? c.n1 + op2.chunks() : c.n1) - 1;
     uint4 a[2][MT][2];
     Parts ap[2];
-    issue_b(c, 0, 0);
-    load_a(c, 0, a[0]);
-    if (c.last > 0) load_a(c, 1, a[1]);
-    else mask(c, 0, a[0]);
+    // chunk 0 into slot U
+    auto first = [&](auto u) {
+      constexpr int U = decltype(u)::value;
+      issue_b(c, 0, U);
+      load_a(c, 0, a[U]);
+      if (c.last > 0) load_a(c, 1, a[U ^ 1]);
+      if (c.n1 == 1) mask(op1.K, 0, a[U]);
 #pragma unroll
-    for (int d = 0; d < MT * 4; ++d) split_pair(a[0], d / 4, d % 4, amax, ap[0]);
+      for (int d = 0; d < MT * 4; ++d) split_pair(a[U], d / 4, d % 4, amax, ap[U]);
+    };
+    // The last chunk is always in slot 1, so that there is one tail: with three,
+    // one per remainder, the accumulators of a tail took registers beside the
+    // loop's (213 instead of 145 for 1 x 8 tiles).
+    typedef std::integral_constant<int, 0> Slot0;
+    typedef std::integral_constant<int, 1> Slot1;
     int i = 0;
-    for (; i + 3 <= c.last; i += 2) {
-      step<0, true, false, false, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
-      step<1, true, false, false, FROM, SHIFT, NA>(c, i + 1, a, ap, amax, acc);
-    }
-    const int left = c.last - i;  // 0, 1 or 2 more chunks after chunk i
-    if (left == 2) {
-      step<0, true, false, false, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
-      step<1, false, true, false, FROM, SHIFT, NA>(c, i + 1, a, ap, amax, acc);
-      step<0, false, false, true, FROM, SHIFT, NA>(c, i + 2, a, ap, amax, acc);
-    } else if (left == 1) {
-      step<0, false, true, false, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
-      step<1, false, false, true, FROM, SHIFT, NA>(c, i + 1, a, ap, amax, acc);
+    if (!CONCAT && c.last == 0) {
+      first(Slot0{});
+      step<0, false, false, true, FROM, SHIFT, NA>(c, i, op1, a, ap, amax, acc, lo);
     } else {
-      step<0, false, false, true, FROM, SHIFT, NA>(c, i, a, ap, amax, acc);
+      if (c.last % 2 == 0) {
+        first(Slot1{});
+        step<1, true, false, false, FROM, SHIFT, NA>(c, i++, op1, a, ap, amax, acc, lo);
+      } else {
+        first(Slot0{});
+      }
+      for (; i + 1 < c.last; i += 2) {
+        step<0, true, false, false, FROM, SHIFT, NA>(c, i, op1, a, ap, amax, acc, lo);
+        step<1, true, false, false, FROM, SHIFT, NA>(c, i + 1, op1, a, ap, amax, acc, lo);
+      }
+      step<0, false, true, false, FROM, SHIFT, NA>(c, i, op1, a, ap, amax, acc, lo);
+      step<1, false, false, true, FROM, SHIFT, NA>(c, i + 1, op1, a, ap, amax, acc, lo);
     }
     ring_barrier();  // the stages may be refilled by a following phase
   }
 
+  // acc += lo
+  template <int NA>
+  __device__ __forceinline__ static void finish(f32x4 (&acc)[MT][NA], const f32x4 (&lo)[MT][NA]) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int t = 0; t < NA; ++t) acc[mt][t] += lo[mt][t];
+  }
   // does this wave meet a row outside the split's range (uniform per wave)
   __device__ __forceinline__ static bool special(const float (&amax)[MT]) {
     bool sp = false;
@@ -290,17 +342,16 @@ struct Split3 {
   // acc += A rows x W with the float32 instruction, operands straight from
   // memory: the waves whose values the split does not take (rare, not tuned)
   template <int FROM = NT, int SHIFT = 0, int NA = NT>
-  __device__ __forceinline__ static void native_phase(
-      const float* __restrict__ A, int64_t lda, int64_t M, const WSrc& w, int64_t n0, int64_t tile0,
-      f32x4 (&acc)[MT][NA], const int32_t* __restrict__ arow = nullptr) {
+  __device__ __forceinline__ static void native_phase(const Rows& o, int64_t M, const WSrc& w, int64_t n0,
+                                                      int64_t tile0, f32x4 (&acc)[MT][NA]) {
     const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
     int64_t off[MT];
-    row_offsets(arow, lda, M, tile0 + (threadIdx.x >> 6) * MT * 16, off);
+    row_offsets(o.arow, o.lda, M, tile0 + (threadIdx.x >> 6) * MT * 16, off);
     for (int64_t k0 = 0; k0 < w.K; k0 += 4) {
       const int64_t k = k0 + lg;
       float a[MT], b[NT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) a[mt] = k < w.K ? A[off[mt] + k] : 0.0f;
+      for (int mt = 0; mt < MT; ++mt) a[mt] = k < w.K ? o.a[off[mt] + k] : 0.0f;
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) b[nt] = w.at(k, n0 + nt * 16 + lr);
 #pragma unroll
@@ -323,7 +374,8 @@ struct Split3 {
 constexpr int kPackThreads = 256, kPackChunks = kPackThreads / 64;
 __host__ __device__ inline int64_t pack_parts(int64_t nch) { return (nch + kPackChunks - 1) / kPackChunks; }
 struct PackOut {
-  uint4* img;
+  uint4* img;  // column block b's image begins b * stride chunks further on
+  int stride;
   int32_t* flags;
 };
 __global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1, WSrc w2, PackOut o2,
@@ -336,7 +388,7 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1
   w.w += (int64_t)grp * w.K * w.ldw;
   const int nch = (int)((w.K + 31) / 32), tile = blockIdx.x, tiles = gridDim.x;
   const int b = tile / nt, t = tile % nt;
-  uint4* im = o.img + ((int64_t)grp * tiles * nch + (int64_t)b * nt * nch) * 192;
+  uint4* im = o.img + ((int64_t)grp * (tiles / nt) + b) * o.stride * nt * 192;
   const int part = blockIdx.z;
   if (part >= pack_parts(nch)) return;
   if (threadIdx.x < 16) cmax[threadIdx.x] = 0;
@@ -406,9 +458,9 @@ __device__ __forceinline__ bool any_flag(const int32_t* __restrict__ flags, int6
 // float32 PLAIN / CONCAT / grouped through Split3.  The column blocks of one
 // row block run on one XCD one after another (workgroup w goes to XCD w % 8),
 // so that its rows of A come from HBM once.  GROUPED as k_gemm_grouped below.
-template <int MT, int NT, int NW, bool GROUPED>
+template <int MT, int NT, int NW, bool GROUPED, bool CONCAT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(GemmArgs g, int ny) {
-  typedef Split3<MT, NT, NW> R;
+  typedef Split3<MT, NT, NW, CONCAT> R;
   __shared__ uint4 ring[R::RING_SLOTS];
   if constexpr (GROUPED)
     if ((g.err1 && *g.err1) || (g.err2 && *g.err2)) return;
@@ -430,35 +482,33 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   } else if (tile0 >= g.M) {
     return;
   }
-  f32x4 acc[MT][NT];
+  f32x4 acc[MT][NT], lo[MT][NT];
   float amax[MT];
-  auto clear = [&] {
+  auto clear = [](f32x4 (&x)[MT][NT]) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < NT; ++nt) x[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
-  clear();
+  clear(acc);
+  clear(lo);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) amax[mt] = 0.0f;
-  const float *A = static_cast<const float*>(g.a), *A2 = static_cast<const float*>(g.a2);
-  const int32_t* arow = GROUPED ? g.arow : nullptr;
-  const int64_t nch = (g.K + 31) / 32, nch2 = (g.K2 + 31) / 32;
-  const uint4* wi = static_cast<const uint4*>(g.wt) + ((int64_t)grp * ny + y) * nch * R::STAGE;
-  const bool concat = !GROUPED && g.mode == SAGA_GEMM_CONCAT;
-  for (int ph = 0; ph < (concat ? 2 : 1); ++ph)
-    R::phase(ph ? A2 : A, ph ? g.lda2 : g.lda, g.M, ph ? g.K2 : g.K,
-             ph ? static_cast<const uint4*>(g.wt2) + (int64_t)y * nch2 * R::STAGE : wi, tile0, ring,
-             amax, acc, arow);
+  const typename R::Rows op1{static_cast<const float*>(g.a), g.lda, g.K, GROUPED ? g.arow : nullptr};
+  const typename R::Rows op2{static_cast<const float*>(g.a2), g.lda2, CONCAT ? g.K2 : 0, nullptr};
+  const int64_t nch = (g.K + 31) / 32, nch2 = CONCAT ? (g.K2 + 31) / 32 : 0;
+  const int64_t blk = (int64_t)grp * ny + y;
+  R::phase(op1, op2, g.M, static_cast<const uint4*>(g.wt) + blk * (nch + nch2) * R::STAGE, tile0, ring, amax, acc, lo);
+  R::finish(acc, lo);
   bool slow = R::special(amax);
-  slow |= any_flag<NT>(g.wflags, (int64_t)grp * ny + y, nch);
-  if (concat) slow |= any_flag<NT>(g.wflags2, y, nch2);
+  slow |= any_flag<NT>(g.wflags, blk, nch);
+  if (CONCAT) slow |= any_flag<NT>(g.wflags2, y, nch2);
   if (slow) {
-    clear();
+    clear(acc);
     WSrc w = wsrc1(g);
     w.w += (int64_t)grp * g.K * g.ldw;
-    R::native_phase(A, g.lda, g.M, w, n0, tile0, acc, arow);
-    if (concat) R::native_phase(A2, g.lda2, g.M, wsrc2(g), n0, tile0, acc);
+    R::native_phase(op1, g.M, w, n0, tile0, acc);
+    if (CONCAT) R::native_phase(op2, g.M, wsrc2(g), n0, tile0, acc);
   }
   const int64_t row0 = tile0 + wave * MT * 16;
   if constexpr (GROUPED) {
@@ -482,30 +532,33 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 // add up in the same accumulators; only the n blocks are kept apart.
 template <int NT3>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_gru_split(GemmArgs g) {
-  constexpr int NT = 3 * NT3, NA = 4 * NT3;
+  constexpr int NT = 3 * NT3, NA = 4 * NT3, F = 16 * NT3;
   typedef Split3<1, NT, 4> R;
   __shared__ uint4 ring[R::RING_SLOTS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t tile0 = (int64_t)blockIdx.x * R::BM;
-  const float *A = static_cast<const float*>(g.a), *h = static_cast<const float*>(g.a2);
-  f32x4 acc[1][NA];
-  auto clear = [&] {
+  const float* h = static_cast<const float*>(g.a2);
+  f32x4 acc[1][NA], lo[1][NA];
+  auto clear = [](f32x4 (&x)[1][NA]) {
 #pragma unroll
-    for (int t = 0; t < NA; ++t) acc[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NA; ++t) x[0][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
-  clear();
+  clear(acc);
+  clear(lo);
   float amax[1] = {0.0f};
-  R::template phase<NT, 0, NA>(A, g.lda, g.M, g.K, static_cast<const uint4*>(g.wt), tile0, ring, amax, acc);
-  R::template phase<2 * NT3, NT3, NA>(h, g.lda2, g.M, g.K2, static_cast<const uint4*>(g.wt2), tile0, ring,
-                                      amax, acc);
+  const typename R::Rows op1{static_cast<const float*>(g.a), g.lda, g.K, nullptr}, op2{h, g.lda2, F, nullptr};
+  // (K2 = F, so the second product's chunks are known here)
+  R::template phase<NT, 0, 0, NA>(op1, op2, g.M, static_cast<const uint4*>(g.wt), tile0, ring, amax, acc, lo);
+  R::template phase<2 * NT3, NT3, (F + 31) / 32, NA>(op2, op2, g.M, static_cast<const uint4*>(g.wt2), tile0, ring, amax,
+                                                     acc, lo);
+  R::finish(acc, lo);
   bool slow = R::special(amax);
-  slow |= any_flag<NT>(g.wflags, 0, (g.K + 31) / 32) || any_flag<NT>(g.wflags2, 0, (g.K2 + 31) / 32);
+  slow |= any_flag<NT>(g.wflags, 0, (g.K + 31) / 32) || any_flag<NT>(g.wflags2, 0, (F + 31) / 32);
   if (slow) {
-    clear();
-    R::template native_phase<NT, 0, NA>(A, g.lda, g.M, wsrc1(g), 0, tile0, acc);
-    R::template native_phase<2 * NT3, NT3, NA>(h, g.lda2, g.M, wsrc2(g), 0, tile0, acc);
+    clear(acc);
+    R::template native_phase<NT, 0, NA>(op1, g.M, wsrc1(g), 0, tile0, acc);
+    R::template native_phase<2 * NT3, NT3, NA>(op2, g.M, wsrc2(g), 0, tile0, acc);
   }
-  constexpr int F = NT3 * 16;
   const int64_t row0 = tile0 + wave * 16;
   float* out = static_cast<float*>(g.out);
   // biases and previous states are all loaded before the first store (a
@@ -558,13 +611,13 @@ SplitShape split_shape(int64_t N, int64_t K, int groups, int mode) {
   return s;
 }
 
-template <int MT, int NT, int NW, bool GROUPED>
+template <int MT, int NT, int NW, bool GROUPED, bool CONCAT = false>
 hipError_t launch_split(const GemmArgs& g, int ny, hipStream_t st) {
-  typedef Split3<MT, NT, NW> R;
+  typedef Split3<MT, NT, NW, CONCAT> R;
   static_assert(R::LDS_BYTES <= 160 * 1024, "LDS ring too large");
   const int64_t mt = (g.M + R::BM - 1) / R::BM;
   const unsigned grid = (unsigned)((mt + kXcds - 1) / kXcds * kXcds * ny);
-  hipLaunchKernelGGL((k_gemm_split<MT, NT, NW, GROUPED>), dim3(grid), dim3(R::THREADS), 0, st, g,
+  hipLaunchKernelGGL((k_gemm_split<MT, NT, NW, GROUPED, CONCAT>), dim3(grid), dim3(R::THREADS), 0, st, g,
                      ny);
   return hipGetLastError();
 }
@@ -583,7 +636,10 @@ hipError_t dispatch_split_nt(const GemmArgs& g, const SplitShape& s, int64_t chu
   if constexpr (GROUPED)  // tiles of exactly kRelTile rows
     return tall ? launch_split<2, NT, 4, true>(g, s.ny, st) : launch_split<1, NT, 8, true>(g, s.ny, st);
   else
-    return tall ? launch_split<2, NT, 4, false>(g, s.ny, st) : launch_split<1, NT, 4, false>(g, s.ny, st);
+    if (g.mode == SAGA_GEMM_CONCAT)
+      return tall ? launch_split<2, NT, 4, false, true>(g, s.ny, st) : launch_split<1, NT, 4, false, true>(g, s.ny, st);
+    else
+      return tall ? launch_split<2, NT, 4, false>(g, s.ny, st) : launch_split<1, NT, 4, false>(g, s.ny, st);
 }
 
 template <bool GROUPED>
@@ -611,7 +667,7 @@ size_t split_workspace_bytes(int mode, int64_t N, int64_t K, int64_t K2, int gro
   return (size_t)(s.img_bytes + s2.img_bytes + s.flag_bytes + s2.flag_bytes);
 }
 
-// Workspace: the image of w, the image of w2, then the flags of each
+// Workspace: the images of w and w2 (column block by column block), then the flags of each
 hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
   const bool grouped = g0.groups > 0, gru = !grouped && g0.mode == SAGA_GEMM_GRU;
   const bool two = !grouped && g0.mode != SAGA_GEMM_PLAIN;
@@ -623,18 +679,19 @@ hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
     return hipErrorInvalidValue;
   GemmArgs g = g0;
   char* ws = static_cast<char*>(g.ws);
-  char* fl = ws + s.img_bytes + s2.img_bytes;
-  g.wt = ws;
-  g.wt2 = ws + s.img_bytes;
-  int32_t* f1 = reinterpret_cast<int32_t*>(fl);
-  int32_t* f2 = reinterpret_cast<int32_t*>(fl + s.flag_bytes);
+  int32_t* f1 = reinterpret_cast<int32_t*>(ws + s.img_bytes + s2.img_bytes);
+  int32_t* f2 = f1 + s.flag_bytes / 4;
   g.wflags = f1;
   g.wflags2 = f2;
+  uint4* img = reinterpret_cast<uint4*>(ws);
+  uint4* img2 = img + s.nch * s.nt * 192;  // behind the first column block of w
+  g.wt = img;
+  g.wt2 = img2;
+  const int stride = (int)(s.nch + s2.nch);
   const unsigned parts = (unsigned)pack_parts(s.nch > s2.nch ? s.nch : s2.nch);
   hipLaunchKernelGGL(k_pack_split, dim3((unsigned)(s.ny * s.nt), (unsigned)(groups + (two ? 1 : 0)), parts),
-                     dim3(kPackThreads), 0, st, wsrc1(g),
-                     PackOut{reinterpret_cast<uint4*>(ws), f1}, wsrc2(g),
-                     PackOut{reinterpret_cast<uint4*>(ws + s.img_bytes), f2}, groups, s.nt);
+                     dim3(kPackThreads), 0, st, wsrc1(g), PackOut{img, stride, f1}, wsrc2(g),
+                     PackOut{img2, stride, f2}, groups, s.nt);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (gru) {
