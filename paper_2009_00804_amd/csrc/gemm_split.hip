@@ -8,9 +8,11 @@ namespace saga {
 namespace {
 
 // ---------------------------------------------------------------------------
-// float32 products on the bfloat16 matrix cores.  Every float32 value is the
-// exact sum of three bfloat16 values, x = x1 + x2 + x3 (round to nearest, then
-// the remainders: 8 + 8 + 8 bits of significand), so
+// float32 products on the bfloat16 matrix cores.  Scaled by 2^16, every float32
+// value below 2^110, subnormals included, is the exact sum of three bfloat16
+// values, x = x1 + x2 + x3 (round to nearest, then the remainders: 8 + 8 + 8
+// bits of significand; the scale keeps the last bit at 2^-133 or above, and the
+// instruction takes subnormal bfloat16 values as they are).  Then
 //   a w = a1 w1 + (a1 w2 + a2 w1) + (a1 w3 + a2 w2 + a3 w1) + rest
 // with |rest| <= 2^-24.2 |a w|, 2^-27.5 |a w| in the root mean square, and the
 // six products are accumulated in float32 by v_mfma_f32_16x16x32_bf16.  One such
@@ -30,18 +32,19 @@ namespace {
 // after ReLU 3.1e-7 / 3.5e-7 / 1.0e-7, 2 % of values nonzero 6.7e-8 / 1.3e-7 /
 // 3.0e-8.
 //
-// The split needs its operands' magnitudes well inside the float32 range: a
-// row of A (or a column of W) whose largest magnitude is 2^60 or more
-// (infinities included), or below 2^-40 but not zero, would lose what plain
-// float32 keeps.  The kernel tracks every row's largest magnitude as it loads
-// the row and k_pack_split notes such columns per 16-column tile; a wave that
-// meets either recomputes its tile with the float32 instruction
-// (native_phase).  NaN gives NaN either way.
+// Range.  The scaled sums must stay finite: with m the largest magnitude of a
+// wave's rows and w of its columns, m < 2^110, w < 2^110 and m w K < 2^94.  The
+// kernel tracks the rows' as it loads them, k_pack_split notes the columns'; a
+// wave that meets more (infinities included), or NaN weights, recomputes its
+// tile with the float32 instruction (native_phase; 262144 x 256 x 128, us: 114,
+// every 1000th row infinite 198, every row 443).  NaN in A gives NaN either way.
 // ---------------------------------------------------------------------------
-constexpr float kSplitBig = 1152921504606846976.0f;   // 2^60
-constexpr float kSplitSmall = 9.094947017729282e-13f;  // 2^-40
-__device__ __forceinline__ bool split_special(float m) {
-  return !(m < kSplitBig) || (m > 0.0f && m < kSplitSmall);
+constexpr float kSplitScale = 65536.0f;
+constexpr float kSplitUnscale = 1.0f / (kSplitScale * kSplitScale);
+constexpr float kSplitMax = 1298074214633706907132624082305024.0f;  // 2^110
+constexpr float kSplitSum = 19807040628566084398385987584.0f;       // 2^94
+__device__ __forceinline__ bool split_special(float m, float w, float k) {
+  return !(m < kSplitMax && w < kSplitMax && m * w * k < kSplitSum);
 }
 
 typedef __attribute__((address_space(3))) uint4 lds_uint4;
@@ -49,8 +52,9 @@ typedef __attribute__((address_space(3))) uint4 lds_uint4;
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// x = p[0] + p[1] + p[2], two values at a time
+// kSplitScale x = p[0] + p[1] + p[2], two values at a time
 __device__ __forceinline__ void split3(f32x2 x, uint32_t (&p)[3]) {
+  x *= kSplitScale;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     const bf16x2 h = __builtin_convertvector(x, bf16x2);
@@ -318,24 +322,28 @@ struct Split3 {
     ring_barrier();  // the stages may be refilled by a following phase
   }
 
-  // acc += lo
+  // acc += lo, without the scale
   template <int NA>
   __device__ __forceinline__ static void finish(f32x4 (&acc)[MT][NA], const f32x4 (&lo)[MT][NA]) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int t = 0; t < NA; ++t) acc[mt][t] += lo[mt][t];
+      for (int t = 0; t < NA; ++t) acc[mt][t] = (acc[mt][t] + lo[mt][t]) * kSplitUnscale;
   }
-  // does this wave meet a row outside the split's range (uniform per wave)
-  __device__ __forceinline__ static bool special(const float (&amax)[MT]) {
-    bool sp = false;
+  // does this wave meet values outside the split's range (uniform); wbits: this
+  // lane's part of the columns' largest magnitude.  Ordinary ones take two
+  // comparisons, without the columns' reduction over the lanes.
+  __device__ __forceinline__ static bool special(const float (&amax)[MT], uint32_t wbits, int64_t k) {
+    constexpr float kOrdinary = 140737488355328.0f;  // 2^47
+    bool sp = !(__uint_as_float(wbits) * (float)k < kOrdinary);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      float m = amax[mt];
-      m = fmaxf(m, __shfl_xor(m, 16, 64));
-      m = fmaxf(m, __shfl_xor(m, 32, 64));
-      sp |= split_special(m);
-    }
+    for (int mt = 0; mt < MT; ++mt) sp |= !(amax[mt] < kOrdinary);
+    if (!__any(sp)) return false;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) wbits = max(wbits, (uint32_t)__shfl_xor((int)wbits, off, 64));
+    sp = false;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) sp |= split_special(amax[mt], __uint_as_float(wbits), (float)k);
     return __any(sp);
   }
 
@@ -368,19 +376,18 @@ struct Split3 {
 // The image Split3 streams, for one group of weights (blockIdx.y < groups) or
 // the second operand (the next one): for column block b, chunk c, plane q, tile
 // t of the block: 64 pieces of 8 k.  A workgroup takes kPackChunks chunks of a
-// 16-column tile and notes in its own flag whether a column of them is outside
-// the split's range (one workgroup per tile ran 5 to 6 us; a folded tile of 512
-// x 16, eight terms each, 20).
+// 16-column tile and notes their largest magnitude (one workgroup per tile ran 5
+// to 6 us; a folded tile of 512 x 16, eight terms each, 20).
 constexpr int kPackThreads = 256, kPackChunks = kPackThreads / 64;
 __host__ __device__ inline int64_t pack_parts(int64_t nch) { return (nch + kPackChunks - 1) / kPackChunks; }
 struct PackOut {
   uint4* img;  // column block b's image begins b * stride chunks further on
   int stride;
-  int32_t* flags;
+  uint32_t* wmax;
 };
 __global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1, WSrc w2, PackOut o2,
                                                              int groups, int nt) {
-  __shared__ uint32_t cmax[16];
+  __shared__ uint32_t tmax;
   const bool second = (int)blockIdx.y >= groups;
   const int grp = second ? 0 : blockIdx.y;
   WSrc w = second ? w2 : w1;
@@ -391,7 +398,7 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1
   uint4* im = o.img + ((int64_t)grp * (tiles / nt) + b) * o.stride * nt * 192;
   const int part = blockIdx.z;
   if (part >= pack_parts(nch)) return;
-  if (threadIdx.x < 16) cmax[threadIdx.x] = 0;
+  if (threadIdx.x == 0) tmax = 0;
   __syncthreads();
   const int r = threadIdx.x & 15;
   const int64_t n = (int64_t)tile * 16 + r;
@@ -437,22 +444,21 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1
     for (int k = 0; k < 3; ++k)
       im[((int64_t)c * 3 + k) * nt * 64 + t * 64 + p * 16 + r] = make_uint4(q[k][0], q[k][1], q[k][2], q[k][3]);
   }
-  atomicMax(&cmax[r], m);
+  // (as bits: NaN is larger than any value)
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+  if ((threadIdx.x & 63) == 0) atomicMax(&tmax, m);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int sp = 0;
-    for (int j = 0; j < 16; ++j) sp |= split_special(__uint_as_float(cmax[j]));
-    o.flags[((int64_t)grp * tiles + tile) * pack_parts(nch) + part] = sp;
-  }
+  if (threadIdx.x == 0) o.wmax[((int64_t)grp * tiles + tile) * pack_parts(nch) + part] = tmax;
 }
 
-// whether k_pack_split flagged any column of column block b (uniform)
+// this lane's part of the largest magnitude k_pack_split noted for column block b
 template <int NT>
-__device__ __forceinline__ bool any_flag(const int32_t* __restrict__ flags, int64_t b, int64_t nch) {
+__device__ __forceinline__ uint32_t block_max(const uint32_t* __restrict__ wmax, int64_t b, int64_t nch) {
   const int n = NT * (int)pack_parts(nch);
-  int f = 0;
-  for (int i = threadIdx.x & 63; i < n; i += 64) f |= flags[b * n + i];
-  return __any(f != 0);
+  uint32_t m = 0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) m = max(m, wmax[b * n + i]);
+  return m;
 }
 
 // float32 PLAIN / CONCAT / grouped through Split3.  The column blocks of one
@@ -500,10 +506,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int64_t blk = (int64_t)grp * ny + y;
   R::phase(op1, op2, g.M, static_cast<const uint4*>(g.wt) + blk * (nch + nch2) * R::STAGE, tile0, ring, amax, acc, lo);
   R::finish(acc, lo);
-  bool slow = R::special(amax);
-  slow |= any_flag<NT>(g.wflags, blk, nch);
-  if (CONCAT) slow |= any_flag<NT>(g.wflags2, y, nch2);
-  if (slow) {
+  uint32_t wm = block_max<NT>(g.wmax, blk, nch);
+  if (CONCAT) wm = max(wm, block_max<NT>(g.wmax2, y, nch2));
+  if (R::special(amax, wm, g.K + op2.K)) {
     clear(acc);
     WSrc w = wsrc1(g);
     w.w += (int64_t)grp * g.K * g.ldw;
@@ -552,9 +557,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   R::template phase<2 * NT3, NT3, (F + 31) / 32, NA>(op2, op2, g.M, static_cast<const uint4*>(g.wt2), tile0, ring, amax,
                                                      acc, lo);
   R::finish(acc, lo);
-  bool slow = R::special(amax);
-  slow |= any_flag<NT>(g.wflags, 0, (g.K + 31) / 32) || any_flag<NT>(g.wflags2, 0, (F + 31) / 32);
-  if (slow) {
+  const uint32_t wm = max(block_max<NT>(g.wmax, 0, (g.K + 31) / 32), block_max<NT>(g.wmax2, 0, (F + 31) / 32));
+  if (R::special(amax, wm, g.K + F)) {
     clear(acc);
     R::template native_phase<NT, 0, NA>(op1, g.M, wsrc1(g), 0, tile0, acc);
     R::template native_phase<2 * NT3, NT3, NA>(op2, g.M, wsrc2(g), 0, tile0, acc);
@@ -598,7 +602,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 // cover N, of equal width
 struct SplitShape {
   int nt, ny;
-  int64_t nch, img_bytes, flag_bytes;  // per K operand (and group, for the image)
+  int64_t nch, img_bytes, max_bytes;  // per K operand (and group, for the image)
 };
 SplitShape split_shape(int64_t N, int64_t K, int groups, int mode) {
   SplitShape s;
@@ -607,7 +611,7 @@ SplitShape split_shape(int64_t N, int64_t K, int groups, int mode) {
   s.nt = (tiles + s.ny - 1) / s.ny;
   s.nch = (K + 31) / 32;
   s.img_bytes = (int64_t)groups * s.ny * s.nt * s.nch * 3072;
-  s.flag_bytes = ((int64_t)groups * s.ny * s.nt * pack_parts(s.nch) * 4 + 255) / 256 * 256;
+  s.max_bytes = ((int64_t)groups * s.ny * s.nt * pack_parts(s.nch) * 4 + 255) / 256 * 256;
   return s;
 }
 
@@ -664,10 +668,10 @@ bool gemm_splits(int dtype, int mode, int64_t N, int64_t K) {
 
 size_t split_workspace_bytes(int mode, int64_t N, int64_t K, int64_t K2, int groups) {
   const SplitShape s = split_shape(N, K, groups, mode), s2 = split_shape(N, K2, groups, mode);
-  return (size_t)(s.img_bytes + s2.img_bytes + s.flag_bytes + s2.flag_bytes);
+  return (size_t)(s.img_bytes + s2.img_bytes + s.max_bytes + s2.max_bytes);
 }
 
-// Workspace: the images of w and w2 (column block by column block), then the flags of each
+// Workspace: the images of w and w2 (column block by column block), then the largest magnitudes of each
 hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
   const bool grouped = g0.groups > 0, gru = !grouped && g0.mode == SAGA_GEMM_GRU;
   const bool two = !grouped && g0.mode != SAGA_GEMM_PLAIN;
@@ -679,10 +683,10 @@ hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
     return hipErrorInvalidValue;
   GemmArgs g = g0;
   char* ws = static_cast<char*>(g.ws);
-  int32_t* f1 = reinterpret_cast<int32_t*>(ws + s.img_bytes + s2.img_bytes);
-  int32_t* f2 = f1 + s.flag_bytes / 4;
-  g.wflags = f1;
-  g.wflags2 = f2;
+  uint32_t* m1 = reinterpret_cast<uint32_t*>(ws + s.img_bytes + s2.img_bytes);
+  uint32_t* m2 = m1 + s.max_bytes / 4;
+  g.wmax = m1;
+  g.wmax2 = m2;
   uint4* img = reinterpret_cast<uint4*>(ws);
   uint4* img2 = img + s.nch * s.nt * 192;  // behind the first column block of w
   g.wt = img;
@@ -690,8 +694,8 @@ hipError_t launch_gemm_split(const GemmArgs& g0, hipStream_t st) {
   const int stride = (int)(s.nch + s2.nch);
   const unsigned parts = (unsigned)pack_parts(s.nch > s2.nch ? s.nch : s2.nch);
   hipLaunchKernelGGL(k_pack_split, dim3((unsigned)(s.ny * s.nt), (unsigned)(groups + (two ? 1 : 0)), parts),
-                     dim3(kPackThreads), 0, st, wsrc1(g), PackOut{img, stride, f1}, wsrc2(g),
-                     PackOut{img2, stride, f2}, groups, s.nt);
+                     dim3(kPackThreads), 0, st, wsrc1(g), PackOut{img, stride, m1}, wsrc2(g),
+                     PackOut{img2, stride, m2}, groups, s.nt);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (gru) {

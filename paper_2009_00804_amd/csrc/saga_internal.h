@@ -129,10 +129,10 @@ struct GemmArgs {
   // set by launch_gemm: packed weights in the workspace, ld kp / kp2
   const void* wt; int64_t kp;
   const void* wt2; int64_t kp2;
-  // float32: per 16-column tile of wt / wt2 and part of its k, a column the
-  // split does not take
-  const int32_t* wflags;
-  const int32_t* wflags2;
+  // float32: the largest magnitude (as bits) of every 16-column tile of w / w2
+  // and part of its k
+  const uint32_t* wmax;
+  const uint32_t* wmax2;
   // forms of w that only the float32 split path takes (forms(): either set):
   // wcb > 0: N / wcb column blocks of wcb columns (ld ldw), wcbs apart;
   // fold > 0: w has `fold` columns and N = fold + 2 fold_heads, the rest being

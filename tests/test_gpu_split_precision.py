@@ -55,3 +55,37 @@ def test_no_further_from_float64_than_float32_sums(kind, M, K, K2, N):
     ref = sum(x[pick].astype(np.float64) @ y for x, y in zip(a, w))
     plain = _rms(_fma_sum([(x[pick], y) for x, y in zip(a, w)]), ref)
     assert _rms(got[pick], ref) <= 1.04 * plain
+
+
+def _bound(a, w):
+    """a float32 sum of the split's terms, plus one rounding of a subnormal result"""
+    mag = np.abs(a).astype(np.float64) @ np.abs(w).astype(np.float64)
+    return (a.shape[1] + 6) * 2.0 ** -24 * mag + 2.0 ** -149
+
+
+@pytest.mark.parametrize("e", [60, 105, 112, 120, 126, 130, 140, 148])
+def test_elements_far_below_their_row_and_column(e):
+    """Values down to the smallest subnormal keep their bits beside ordinary ones
+    (here: meet a zero), in either operand."""
+    rng = np.random.default_rng(e)
+    tiny = (rng.uniform(1, 2, 64) * 2.0 ** -e).astype(np.float32)
+    big = (rng.uniform(1, 2, 64) * 2.0 ** 40).astype(np.float32)
+    one = rng.uniform(1, 2, 64).astype(np.float32)
+    zero = np.zeros(64, np.float32)
+    a, w = np.stack([one, tiny], 1), np.stack([zero, big])
+    assert np.all(np.abs(_run(a, w) - a.astype(np.float64) @ w) <= _bound(a, w))
+    a, w = np.stack([zero, big], 1), np.stack([one, tiny])
+    assert np.all(np.abs(_run(a, w) - a.astype(np.float64) @ w) <= _bound(a, w))
+
+
+@pytest.mark.parametrize("ea,ew", [(-45, 0), (0, -45), (-60, -60), (-70, -64), (61, 20), (20, 61), (90, -60), (-100, 109),
+                                   (70, 17), (70, 18), (71, 18), (109, -30), (111, -30), (-30, 111), (100, 20),
+                                   (-140, 30)])
+def test_magnitudes_around_the_split_range(ea, ew):
+    """Small and large operands, on both sides of where the float32 instruction
+    takes over (2^110 in either operand, 2^94 for their product and K)."""
+    rng = np.random.default_rng((ea + 200) * 400 + ew + 200)
+    a = np.ldexp(rng.uniform(0.5, 1, (70, 64)).astype(np.float32) * rng.choice([-1, 1], (70, 64)), ea)
+    w = np.ldexp(rng.uniform(0.5, 1, (64, 48)).astype(np.float32) * rng.choice([-1, 1], (64, 48)), ew)
+    a, w = a.astype(np.float32), w.astype(np.float32)
+    assert np.all(np.abs(_run(a, w) - a.astype(np.float64) @ w) <= _bound(a, w) + 64 * 2.0 ** -149)
