@@ -17,7 +17,8 @@ namespace {
 // with |rest| <= 2^-24.2 |a w|, 2^-27.5 |a w| in the root mean square, and the
 // six products are accumulated in float32 by v_mfma_f32_16x16x32_bf16.  One such
 // instruction takes 32 k at 16 times the rate of v_mfma_f32_16x16x4f32, so six of
-// them take 3/8 of its time.
+// them take 3/8 of its time.  Up to four k the rest is not small beside the sum's own
+// rounding; such a product, which memory bounds, takes all nine terms.
 //
 // Accumulation.  The instruction adds its 32 products to the accumulator eight
 // at a time and rounds after each eight, v_mfma_f32_16x16x4f32 after each
@@ -30,7 +31,7 @@ namespace {
 // three nonzeros per 32 k.)  Relative error against float64, float32 instruction /
 // one accumulator / two, 8192 rows x 128: K = 602 normal 4.4e-7 / 3.7e-7 / 1.3e-7,
 // after ReLU 3.1e-7 / 3.5e-7 / 1.0e-7, 2 % of values nonzero 6.7e-8 / 1.3e-7 /
-// 3.0e-8.
+// 3.0e-8; K = 1 2.5e-8 / 3.3e-8 / 2.5e-8.
 //
 // Range.  The scaled sums must stay finite: with m the largest magnitude of a
 // wave's rows and w of its columns, m < 2^110, w < 2^110 and m w K < 2^94.  The
@@ -39,6 +40,7 @@ namespace {
 // tile with the float32 instruction (native_phase; 262144 x 256 x 128, us: 114,
 // every 1000th row infinite 198, every row 443).  NaN in A gives NaN either way.
 // ---------------------------------------------------------------------------
+constexpr int kAllTerms = 4;
 constexpr float kSplitScale = 65536.0f;
 constexpr float kSplitUnscale = 1.0f / (kSplitScale * kSplitScale);
 constexpr float kSplitMax = 1298074214633706907132624082305024.0f;  // 2^110
@@ -227,8 +229,9 @@ struct Split3 {
       b[q] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(
           Bs + (q * NT + g) * 64 + lane);
   }
-  // Column tile g goes to accumulator g, or g + SHIFT from tile FROM on.
-  template <int U, bool LOAD, bool MASK, bool LAST, int FROM, int SHIFT, int NA>
+  // Column tile g goes to accumulator g, or g + SHIFT from tile FROM on.  NQ: of
+  // the nine products, smallest first, the last NQ; all but the last into `lo`.
+  template <int U, bool LOAD, bool MASK, bool LAST, int FROM, int SHIFT, int NA, int NQ = 6>
   __device__ __forceinline__ static void step(Ctx& c, int i, const Rows& op1, uint4 (&a)[2][MT][2], Parts (&ap)[2],
                                               float (&amax)[MT], f32x4 (&acc)[MT][NA], f32x4 (&lo)[MT][NA]) {
     // chunk i's weights landed (only chunk i + 1's A loads are newer), for
@@ -241,8 +244,7 @@ struct Split3 {
     if constexpr (!LAST) issue_b(c, i + 1, U ^ 1);
     if constexpr (LOAD) load_a(c, i + 2, a[U]);
     __builtin_amdgcn_sched_barrier(0);
-    // smallest products first; all but the last into `lo`
-    constexpr int QA[6] = {2, 1, 0, 1, 0, 0}, QB[6] = {0, 1, 2, 0, 1, 0};
+    constexpr int QA[9] = {2, 2, 1, 2, 1, 0, 1, 0, 0}, QB[9] = {2, 1, 2, 0, 1, 2, 0, 1, 0};
 #pragma unroll
     for (int g = 0; g < NT; ++g) {
       if (g + 1 < NT) read_b(Bs, g + 1, b[(g + 1) & 1]);
@@ -253,11 +255,12 @@ struct Split3 {
         if (g == G0 && i + 2 == c.n1) mask(op1.K, i + 1, a[U ^ 1]);
       }
 #pragma unroll
-      for (int q = 0; q < 6; ++q) {
+      for (int q = 0; q < NQ; ++q) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-          f32x4& d = (q == 5 ? acc : lo)[mt][g + (g >= FROM ? SHIFT : 0)];
-          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part(ap[U], mt, QA[q]), b[g & 1][QB[q]], d, 0, 0, 0);
+          f32x4& d = (q == NQ - 1 ? acc : lo)[mt][g + (g >= FROM ? SHIFT : 0)];
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part(ap[U], mt, QA[9 - NQ + q]), b[g & 1][QB[9 - NQ + q]], d,
+                                                      0, 0, 0);
         }
         if (!LAST && g >= G0) {
           const int slot = (g - G0) * 6 + q;
@@ -304,7 +307,8 @@ struct Split3 {
     int i = 0;
     if (!CONCAT && c.last == 0) {
       first(Slot0{});
-      step<0, false, false, true, FROM, SHIFT, NA>(c, i, op1, a, ap, amax, acc, lo);
+      if (op1.K <= kAllTerms) step<0, false, false, true, FROM, SHIFT, NA, 9>(c, i, op1, a, ap, amax, acc, lo);
+      else step<0, false, false, true, FROM, SHIFT, NA>(c, i, op1, a, ap, amax, acc, lo);
     } else {
       if (c.last % 2 == 0) {
         first(Slot1{});

@@ -89,3 +89,12 @@ def test_magnitudes_around_the_split_range(ea, ew):
     w = np.ldexp(rng.uniform(0.5, 1, (64, 48)).astype(np.float32) * rng.choice([-1, 1], (64, 48)), ew)
     a, w = a.astype(np.float32), w.astype(np.float32)
     assert np.all(np.abs(_run(a, w) - a.astype(np.float64) @ w) <= _bound(a, w) + 64 * 2.0 ** -149)
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4])
+def test_few_k(K):
+    """Up to four k every term counts: a product is rounded as a float32 one is."""
+    rng = np.random.default_rng(K)
+    a, w = rng.standard_normal((4096, K), dtype=np.float32), rng.uniform(-1, 1, (K, 64)).astype(np.float32)
+    ref = a.astype(np.float64) @ w
+    assert _rms(_run(a, w), ref) <= 1.005 * _rms(_fma_sum([(a, w)]), ref)
