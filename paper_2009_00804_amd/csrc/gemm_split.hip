@@ -192,7 +192,7 @@ struct Split3 {
                      :
                      : "s"(__builtin_amdgcn_readfirstlane(dst + s0 * 16)), "v"((uint32_t)(s0 + lane) * 16u),
                        "s"(src)
-                     : "memory");
+                     : "memory", "m0");
     }
   }
 

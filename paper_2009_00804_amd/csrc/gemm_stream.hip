@@ -87,7 +87,7 @@ struct Stream {
                      :
                      : "s"(__builtin_amdgcn_readfirstlane(dst + s0 * 16)), "v"((uint32_t)(s0 + lane) * 16u),
                        "s"(src)
-                     : "memory");
+                     : "memory", "m0");
     }
   }
   // U: register slot of chunk i
