@@ -175,7 +175,17 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
   const bool p_loader = wave * 64 < PV;
   const bool p_lane = wave * 64 + lane < PV;
   const int64_t npos = (int64_t)a.perm_end - a.perm_begin;
-  const uint32_t ring_base = (uint32_t)reinterpret_cast<uintptr_t>((lds_ptr)ring);
+  const uint32_t ring_base = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>((lds_ptr)ring));
+
+  // This wave's pieces of row u into a ring slot.  In assembly: told that the
+  // ring is written, the compiler would wait for every load in flight before
+  // each read of it, stalling each step on the newest prefetch.
+  auto load_p = [&](int u, int slot) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(ring_base + (uint32_t)(slot * G + wave * 256) * 4), "v"(a.gates_x + (int64_t)u * a.ld_gx + (wave * 64 + lane) * 4)
+                 : "memory", "m0");
+  };
 
   int par = 0;
   for (;;) {
@@ -213,10 +223,8 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
       if (p_loader) {
         for (int s = 0; s < kPF; ++s) {
           if (s < d) {
-            const int u = ucache[0][s];
-            if (p_lane)
-              __builtin_amdgcn_global_load_lds(a.gates_x + (int64_t)u * a.ld_gx + (wave * 64 + lane) * 4,
-                                               (lds_ptr)(ring + s * G + wave * 256), 16, 0, 0);
+            const int u = __builtin_amdgcn_readfirstlane(ucache[0][s]);
+            if (p_lane) load_p(u, s);
           }
         }
       }
@@ -229,17 +237,6 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
           else wait_vm_le(d - 1 - s);
         }
         lds_barrier();
-        // this lane's gate-q entry of the step's P row, read with an inline
-        // ds_read_b32 and waited for after the recurrent sum: read as plain
-        // C++, the compiler would first wait for every direct-to-LDS load in
-        // flight (they may write the ring), stalling each step on the newest
-        // prefetch.  The slot has landed: its loader waves waited for it
-        // before the barrier.
-        float pq;
-        asm volatile("ds_read_b32 %0, %1"
-                     : "=v"(pq)
-                     : "v"(ring_base + (uint32_t)(((s % (kPF + 1)) * G + q * H + i) * 4))
-                     : "memory");
         // this lane's values of h: r is h[r / HV * L HV + lane % L * HV + r % HV]
         const float* hb = hbuf[s & 1] + lane % L * HV;
         float hk[HPL];
@@ -250,14 +247,15 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
 #pragma unroll
           for (int j = 0; j < HV; ++j) hk[r + j] = hv[j];
         }
+        // this lane's gate-q entry of the step's P row; the slot has landed: its
+        // loader waves waited for it before the barrier
+        const float pq = ring[(s % (kPF + 1)) * G + q * H + i];
         // the P row of step s + kPF goes to the slot step s - 1 used (read
         // before this step's barrier)
         const int sn = s + kPF;
         if (p_loader && sn < d) {
           const int u = __builtin_amdgcn_readfirstlane(ucache[(sn / kUch) & 1][sn % kUch]);
-          if (p_lane)
-            __builtin_amdgcn_global_load_lds(a.gates_x + (int64_t)u * a.ld_gx + (wave * 64 + lane) * 4,
-                                             (lds_ptr)(ring + (sn % (kPF + 1)) * G + wave * 256), 16, 0, 0);
+          if (p_lane) load_p(u, sn % (kPF + 1));
         }
         __builtin_amdgcn_sched_barrier(0);  // keep every read ahead of the multiply-adds
         float z[L];
@@ -268,7 +266,6 @@ __global__ __launch_bounds__(LstmCfg<H>::THREADS) void k_lstm_gather(LstmArgs a)
 #pragma unroll
           for (int j = 0; j < L; ++j) z[j] = fmaf(w[j][r], hk[r], z[j]);
         reduce_scatter<L / 2>(z);
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(pq) : : "memory");
         const float zq = z[0] + pq;
         // gate q's activation: tanh for g (q == 2, as 2 sigmoid(2x) - 1),
         // sigmoid for i, f, o; then all four to every lane of the quad
