@@ -1346,11 +1346,11 @@ saga_status saga_plan_check(const saga_plan* plan, void* stream, saga_plan_count
       counts->max_in_degree = h[saga::kMaxDegree];
     }
     const int f = h[saga::kErrFlags];
-    if (f & saga::kErrInternal) return fail(SAGA_EINTERNAL, "plan builder invariant violated");
-    if (f)
+    if (f & saga::kErrCsr)  // (the builder's invariants hold for a valid CSR only)
       return fail(SAGA_EGRAPH, "CSR invalid:%s%s%s%s", (f & 1) ? " row_ptr[0]!=0" : "",
                   (f & 2) ? " row_ptr decreasing" : "", (f & 4) ? " row_ptr[num_dst]!=num_edges" : "",
-                  (f & 8) ? " col_idx out of range" : "");
+                  (f & saga::kErrCol) ? " col_idx out of range" : "");
+    if (f) return fail(SAGA_EINTERNAL, "plan builder invariant violated");
     return ok();
   } catch (...) {
     return fail(SAGA_EINTERNAL, "exception");

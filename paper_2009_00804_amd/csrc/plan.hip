@@ -61,6 +61,18 @@ __device__ __forceinline__ int32_t seg_count(int32_t d, int32_t T) { return d > 
 // ------------------------------------------------------------------------
 // kernels
 // ------------------------------------------------------------------------
+// The out-degree count and the row order may run on two streams at once, so
+// neither looks at the errors the other can raise meanwhile: the count at a bad
+// col_idx only, the row order (which never reads col_idx) at everything else.
+// Both were raised by earlier kernels of the reader's own stream, so that every
+// wave reads the same.
+__device__ __forceinline__ bool count_stops(const int32_t* counts) { return counts[kErrFlags] & kErrCol; }
+__device__ __forceinline__ bool order_stops(const int32_t* counts) { return counts[kErrFlags] & ~kErrCol; }
+// for kernels that may themselves raise kErrInternal: one answer per workgroup
+__device__ __forceinline__ bool order_stops_wg(const int32_t* counts) {
+  return __syncthreads_or(threadIdx.x == 0 && order_stops(counts));
+}
+
 __global__ void k_zero(int32_t* p, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -93,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void k_degrees(const int32_t* __restrict_
     if (i < E) {
       int32_t c = col[i];
       if (c < 0 || c >= Vs)
-        err |= 8;
+        err |= kErrCol;
       else
         atomicAdd(&d_out[c], 1);
     }
@@ -299,7 +311,7 @@ __global__ __launch_bounds__(kOdThreads) void k_outdeg_bin(const int32_t* __rest
     const uint32_t rj = ok ? (uint32_t)atomicAdd(&cw[c[j] >> kOdBits], 1) : 0xffffu;
     r[j / 2] = j % 2 ? r[j / 2] | rj << 16 : rj;
   }
-  if (__any(err) && lane == 0) atomicOr(&counts[kErrFlags], 8);
+  if (__any(err) && lane == 0) atomicOr(&counts[kErrFlags], kErrCol);
   __syncthreads();
   {  // exclusive scan over k = b * kOdWaves + w (entry cnt[w * nb + b]):
      // thread t owns k in [t * pk, (t + 1) * pk), then a wave scan and a
@@ -355,7 +367,7 @@ __global__ __launch_bounds__(1024) void k_outdeg_count(const uint16_t* __restric
                                                        int64_t ntiles, int nb, int64_t E,
                                                        int32_t* __restrict__ part,
                                                        const int32_t* counts) {
-  if (counts[kErrFlags]) return;
+  if (count_stops(counts)) return;
   __shared__ int32_t h[kOdBucket];
   constexpr int R = kOdRuns, J = kOdLoads, NW = 1024 / 64;
   // buckets in an XCD-blocked order (gridDim.x = xcd_grid(nb)): XCD x takes
@@ -438,7 +450,7 @@ __global__ __launch_bounds__(1024) void k_outdeg_direct(const int32_t* __restric
       }
     }
   }
-  if (b == 0 && __any(bad) && (threadIdx.x & 63) == 0) atomicOr(&counts[kErrFlags], 8);
+  if (b == 0 && __any(bad) && (threadIdx.x & 63) == 0) atomicOr(&counts[kErrFlags], kErrCol);
   __syncthreads();
   int32_t* pw = part + (int64_t)s * nb * kOdBucket + (int64_t)b * kOdBucket;
   for (int i = threadIdx.x; i < kOdBucket; i += 1024) pw[i] = h[i];
@@ -450,7 +462,7 @@ __global__ __launch_bounds__(kThreads) void k_outdeg_reduce(const int32_t* __res
                                                             int nb, int S, int32_t Vs,
                                                             int32_t* __restrict__ d_out,
                                                             const int32_t* counts) {
-  if (counts[kErrFlags]) return;
+  if (count_stops(counts)) return;
   const int64_t stride = (int64_t)nb * kOdBucket;
   const int64_t n4 = Vs / 4;
   const int64_t g0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, gs = (int64_t)gridDim.x * blockDim.x;
@@ -493,7 +505,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const int32_t* __restri
                                                          int32_t n, int shift,
                                                          int32_t* __restrict__ hist, int64_t ntiles,
                                                          const int32_t* counts) {
-  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
+  if (order_stops(counts) || radix_skips(counts, shift)) return;
   __shared__ int32_t h[kBins];
   const int64_t tile = xcd_tile(ntiles);
   if (tile < 0) return;
@@ -530,7 +542,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
     const int32_t* __restrict__ vals_in, const int32_t* __restrict__ rb_in, int32_t n, int shift,
     const int32_t* __restrict__ offsets, int64_t ntiles, uint32_t* __restrict__ keys_out,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ rb_out, const int32_t* counts) {
-  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
+  if (order_stops_wg(counts) || radix_skips(counts, shift)) return;
   constexpr int NW = kThreads / 64;
   __shared__ int32_t wcnt[NW][kBins];
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
@@ -615,7 +627,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
 __global__ __launch_bounds__(kThreads) void k_scan_reduce(const int32_t* __restrict__ in, int64_t n,
                                                           int32_t* tile_sums, int shift,
                                                           const int32_t* counts) {
-  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
+  if (order_stops(counts) || radix_skips(counts, shift)) return;
   const int64_t base = blockIdx.x * (int64_t)kTile + threadIdx.x * kItems;
   int32_t s = 0;
 #pragma unroll
@@ -629,7 +641,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const int32_t* __restr
 // exclusive scan of the tile sums by one workgroup of 1024 threads
 __global__ __launch_bounds__(1024) void k_scan_tilesums(int32_t* ts, int64_t nt, int shift,
                                                         const int32_t* counts) {
-  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
+  if (order_stops(counts) || radix_skips(counts, shift)) return;
   __shared__ int32_t carry_s;
   if (threadIdx.x == 0) carry_s = 0;
   __syncthreads();
@@ -650,7 +662,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t* in, int6
                                                          const int32_t* tile_sums,
                                                          int32_t* out, int shift,
                                                          const int32_t* counts) {
-  if (counts[kErrFlags] || radix_skips(counts, shift)) return;
+  if (order_stops(counts) || radix_skips(counts, shift)) return;
   const int64_t base = blockIdx.x * (int64_t)kTile + threadIdx.x * kItems;
   int32_t v[kItems];
   int32_t s = 0;
@@ -690,7 +702,7 @@ constexpr int64_t kSumTiles = 4096;  // more tiles: their sums are scanned by a 
 __global__ __launch_bounds__(kSegTile) void k_seg_sums(Order o, int32_t V, int32_t T, int32_t c,
                                                        int32_t* __restrict__ sums, int64_t ntiles,
                                                        const int32_t* counts) {
-  if (counts[kErrFlags]) return;
+  if (order_stops(counts)) return;
   const uint32_t* __restrict__ keys = o.keys[(radix_passes(counts) - 1) & 1];
   int32_t ns = 0, cost = 0;
   const int64_t i = blockIdx.x * (int64_t)kSegTile + threadIdx.x;
@@ -718,7 +730,7 @@ __global__ __launch_bounds__(kSegTile) void k_seg_emit(Order o, int32_t V, int32
                                                        int32_t* __restrict__ seg_beg,
                                                        int32_t* __restrict__ seg_end,
                                                        int32_t* __restrict__ block_ptr, int32_t* counts) {
-  if (counts[kErrFlags]) return;
+  if (order_stops_wg(counts)) return;
   __shared__ int32_t s_deg[kSegTile], s_row[kSegTile], s_rb[kSegTile], s_first[kSegTile + 1], s_cost[kSegTile];
   const int64_t tile = blockIdx.x;
   const int t = threadIdx.x;

@@ -19,8 +19,10 @@ enum Count : int {
   kMaxDegree = 5,
   kCountSlots = 8
 };
-// error bits in counts[kErrFlags]: 1, 2, 4, 8 are CSR errors (see saga.h);
-// this one marks a broken internal invariant of the plan builder
+// error bits in counts[kErrFlags]: 1, 2, 4, 8 are CSR errors (see saga.h; 8:
+// col_idx out of range); kErrInternal marks a broken internal invariant of the
+// plan builder
+constexpr int kErrCol = 8, kErrCsr = 15;
 constexpr int kErrInternal = 1 << 16;
 
 // ---- plan.hip ----

@@ -68,3 +68,34 @@ def test_out_degree_paths(num_src, E):
     deg = np.full(V, E // V)
     deg[3] += E - deg.sum()
     _check(deg, num_src, 512, 4096)
+
+
+@pytest.mark.parametrize("num_src,E", [(50, 4000), (131072 * 3, 12000000)])
+def test_a_bad_source_id_does_not_reach_the_row_order(num_src, E):
+    """Out-degrees and row order may run on two streams: an id out of range,
+    found by the former, changes nothing in the latter and is what is reported."""
+    from gpu_util import lib
+
+    S, V, T, B = lib(), 700, 64, 256
+    deg = np.full(V, E // V)
+    deg[5] += E - deg.sum()
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    col = np.random.default_rng(1).integers(0, num_src, E)
+    ref, _, _ = _plan(rp, col, num_src, T, B)
+    col[E // 2] = num_src
+    g = graph(rp, col, num_src=num_src, seg_len=T, block_cost=B, check=False)
+    st, g.counts = S.saga_plan_check(g.plan, S.stream_handle())
+    assert st == S.SAGA_EGRAPH and g.counts.error_flags == 8
+    got = g.arrays()
+    for k in ("d_in", "perm", "row_seg_first", "seg_row", "seg_beg", "seg_end", "block_ptr"):
+        assert np.array_equal(got[k].cpu().numpy(), ref[k]), k
+
+
+def test_a_bad_graph_is_reported_ahead_of_a_broken_invariant():
+    from gpu_util import lib
+
+    S = lib()
+    g = graph([0, 1, 2], [1, 0])
+    for flags, status in ((8 | 1 << 16, S.SAGA_EGRAPH), (1 << 16, S.SAGA_EINTERNAL)):
+        g._view(g.plan.counts, 8)[4] = flags
+        assert S.saga_plan_check(g.plan, S.stream_handle())[0] == status
