@@ -381,7 +381,9 @@ struct Split3 {
 // the second operand (the next one): for column block b, chunk c, plane q, tile
 // t of the block: 64 pieces of 8 k.  A workgroup takes kPackChunks chunks of a
 // 16-column tile and notes their largest magnitude (one workgroup per tile ran 5
-// to 6 us; a folded tile of 512 x 16, eight terms each, 20).
+// to 6 us; a folded tile of 512 x 16, eight terms each, 20).  A tile of few folded
+// columns divides every sum among its lanes (one head of 64 columns on two lanes
+// alone: a pair of GAT layers at 1,785 vertices, 40 features 68.3 us, now 50.0).
 constexpr int kPackThreads = 256, kPackChunks = kPackThreads / 64;
 __host__ __device__ inline int64_t pack_parts(int64_t nch) { return (nch + kPackChunks - 1) / kPackChunks; }
 struct PackOut {
@@ -406,29 +408,38 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_split(WSrc w1, PackOut o1
   __syncthreads();
   const int r = threadIdx.x & 15;
   const int64_t n = (int64_t)tile * 16 + r;
-  const bool folded = w.fold > 0 && n >= w.fold && n < w.N;
-  // column n (a plain or a block's), or the folded one's first term
-  const int D = folded ? w.fold / w.heads : 1, h = folded ? (int)(n - w.fold) % w.heads : 0;
-  const float* att = folded ? (n - w.fold < w.heads ? w.al : w.ar) + h * D : nullptr;
-  const float* col = w.w + (folded ? h * D : w.cb > 0 ? (int)n / (int)w.cb * w.cbs + (int)n % (int)w.cb : n);
+  // folded columns [f0, f0 + fc) of this tile, fs of its 16 lanes to a sum
+  const int f0 = max(w.fold - tile * 16, 0), fc = w.fold > 0 ? (int)min(w.N - (int64_t)tile * 16, (int64_t)16) - f0 : 0;
+  const bool folded = fc > 0 && r >= f0 && n < w.N;
+  const float* col = w.w + (w.cb > 0 ? (int)n / (int)w.cb * w.cbs + (int)n % (int)w.cb : n);
   const int64_t kn = n < w.N ? w.K : 0;
   uint32_t m = 0;
   const int c = part * kPackChunks + threadIdx.x / 64, p = (threadIdx.x / 16) % 4;
   if (c < nch) {
     const int64_t k0 = (int64_t)c * 32 + p * 4;  // and k0 + 16
     float x[8];
-    if (folded) {
-      // eight k at a time, so that their loads overlap
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+    for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+    if (fc > 0) {  // (uniform in the workgroup)
+      const int fs = fc > 8 ? 1 : fc > 4 ? 2 : fc > 2 ? 4 : 8, D = w.fold / w.heads;
+      const int f = tile * 16 + f0 - w.fold + min(r / fs, fc - 1), h = f % w.heads;
+      const float* wf = w.w + h * D;
+      const float* att = (f < w.heads ? w.al : w.ar) + h * D;
+      // eight k at a time, so that their loads overlap
 #pragma unroll 4
-      for (int d = 0; d < D; ++d)
+      for (int d = r % fs; d < D; d += fs)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int64_t k = k0 + e % 4 + 16 * (e / 4);
-          x[e] += (k < kn ? col[k * w.ldw + d] : 0.0f) * att[d];
+          x[e] += (k < w.K ? wf[k * w.ldw + d] : 0.0f) * att[d];
         }
-    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        for (int off = fs / 2; off > 0; off >>= 1) x[e] += __shfl_xor(x[e], off, 16);
+        x[e] = __shfl(x[e], max(r - f0, 0) * fs, 16);
+      }
+    }
+    if (!folded) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int64_t k = k0 + e % 4 + 16 * (e / 4);
