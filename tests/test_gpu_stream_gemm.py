@@ -47,3 +47,29 @@ def test_products(M, K, K2, N, split):
     ref = sum(_bf(x) @ _bf(y) for x, y in zip(a, w)) + b
     mag = sum(np.abs(_bf(x)) @ np.abs(_bf(y)) for x, y in zip(a, w)) + np.abs(b)
     assert np.all(np.abs(got - ref) <= (K + K2 + 2) * 2.0 ** -24 * mag + 2.0 ** -8 * np.abs(ref) + 1e-30)
+
+
+@pytest.mark.parametrize("M,K,K2,N", [(131072, 70, 0, 140), (131072 + 77, 65, 0, 160), (131073, 130, 66, 170),
+                                      (140000, 72, 40, 190), (131072, 200, 0, 208), (150001, 129, 64, 200)])
+def test_products_of_many_rows(M, K, K2, N):
+    """9 to 13 column tiles over 131,072 rows and more: eight waves a workgroup.
+    A thousand rows are compared, the last tile's among them."""
+    rng = np.random.default_rng(M + K + K2 + N)
+    a = [rng.standard_normal((M, k), dtype=np.float32) for k in (K, K2) if k]
+    w = [rng.uniform(-1, 1, (k, N)).astype(np.float32) for k in (K, K2) if k]
+    op = S.saga_gemm_op()
+    op.dtype, op.mode = S.SAGA_BF16, S.SAGA_GEMM_CONCAT if K2 else S.SAGA_GEMM_PLAIN
+    out = S.padded_empty(M, N, torch.bfloat16, DEV)
+    out.fill_(float("nan"))
+    ad = [dev_padded(x, torch.bfloat16) for x in a] + [None]
+    wd = [torch.from_numpy(x).to(DEV).to(torch.bfloat16) for x in w] + [None]
+    ws = S.workspace(S.saga_apply_vertex_workspace_size(op, K, K2, N), DEV)
+    print(f"stream {M} x {K}+{K2} x {N}", flush=True)
+    S.saga_apply_vertex(op, S.cmat(ad[0]), S.cmat(wd[0]), S.cmat(ad[1]), S.cmat(wd[1]), None, None, S.mat(out),
+                        S._ptr(ws), ws.numel(), S.stream_handle())
+    assert not bool(torch.isnan(out).any())
+    rows = np.unique(np.concatenate([np.arange(130), rng.integers(0, M, 800), np.arange(M - 130, M)]))
+    got = to_np(out[torch.from_numpy(rows).to(DEV)])
+    ref = sum(_bf(x[rows]) @ _bf(y) for x, y in zip(a, w))
+    mag = sum(np.abs(_bf(x[rows])) @ np.abs(_bf(y)) for x, y in zip(a, w))
+    assert np.all(np.abs(got - ref) <= (K + K2 + 2) * 2.0 ** -24 * mag + 2.0 ** -8 * np.abs(ref) + 1e-30)
