@@ -16,7 +16,6 @@ from __future__ import annotations
 
 import argparse
 import ctypes as C
-import hashlib
 import json
 import os
 import statistics
@@ -36,15 +35,11 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def src_sha(name):
-    p = os.path.join(ROOT, "paper_2009_00804_amd", "csrc", name)
-    with open(p, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
-
-
 def load_traffic(kernel, dtype):
     """Per-launch HBM bytes of `kernel` from the counter summary in
-    profiles/, if it was taken on the current kernel source."""
+    profiles/, if it was taken on the current kernel sources."""
+    from paper_2009_00804_amd.profiling import src_sha
+
     p = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(p):
         return None

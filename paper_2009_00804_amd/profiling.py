@@ -49,8 +49,8 @@ import re
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 
-# stage -> ({dtype: [(kernel-name prefix, dispatches per launch, cycle,
-# slots), ...]}, source file).  A kernel that several stages of one step
+# stage -> {dtype: [(kernel-name prefix, dispatches per launch, cycle,
+# slots), ...]}.  A kernel that several stages of one step
 # launch (the same instance serves the layer-1 slices and the layer-2
 # whole-line pass) is split by position: of every `cycle` consecutive
 # dispatches of it, the stage takes those at `slots`.  gather1 runs one
@@ -60,27 +60,46 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 STAGES = {
     # the plan's out-degree count (tile sort by bucket, per-bucket count,
     # partial sums), once per step
-    "outdeg": ({dt: [("k_outdeg_bin", 1, 1, (0,)), ("k_outdeg_count", 1, 1, (0,)),
-                     ("k_outdeg_reduce", 1, 1, (0,))] for dt in ("f32", "bf16")},
-               "plan.hip"),
-    "gather1": ({"f32": [("k_gather_sum<float, 8, 1, 4, 4, true>", 4, 5, (0, 1, 2, 3)),
-                         ("k_combine<float>", 1, 3, (0,))],
-                 "bf16": [("k_gather_sum<unsigned short, 8, 1, 4, 4, true>", 2, 2, (0, 1)),
-                          ("k_combine<unsigned short>", 1, 2, (0,))]},
-                "gather.hip"),
-    "gather2": ({"f32": [("k_gather_sum<float, 8, 1, 4, 4, true>", 1, 5, (4,)),
-                         ("k_gather_sum<float, 4, 1, 4, 8, false>", 1, 1, (0,)),
-                         ("k_combine<float>", 2, 3, (1, 2))],
-                 "bf16": [("k_gather_sum<unsigned short, 8, 1, 4, 4, false>", 1, 1, (0,)),
-                          ("k_combine<unsigned short>", 1, 2, (1,))]},
-                "gather.hip"),
-    "gemm1": ({"f32": [("k_gemm_split<2, 8, 4,", 1, 1, (0,))],
-               "bf16": [("k_gemm_bres<2, 8, 3>", 1, 1, (0,))]},
-              "gemm.hip"),
-    "gemm2": ({"f32": [("k_gemm_split<1, 3, 4,", 1, 1, (0,))],
-               "bf16": [("k_gemm<unsigned short, 2, 3,", 1, 1, (0,))]},
-              "gemm.hip"),
+    "outdeg": {dt: [("k_outdeg_bin", 1, 1, (0,)), ("k_outdeg_count", 1, 1, (0,)),
+                    ("k_outdeg_reduce", 1, 1, (0,))] for dt in ("f32", "bf16")},
+    "gather1": {"f32": [("k_gather_sum<float, 8, 1, 4, 4, true>", 4, 5, (0, 1, 2, 3)),
+                        ("k_combine<float>", 1, 3, (0,))],
+                "bf16": [("k_gather_sum<unsigned short, 8, 1, 4, 4, true>", 2, 2, (0, 1)),
+                         ("k_combine<unsigned short>", 1, 2, (0,))]},
+    "gather2": {"f32": [("k_gather_sum<float, 8, 1, 4, 4, true>", 1, 5, (4,)),
+                        ("k_gather_sum<float, 4, 1, 4, 8, false>", 1, 1, (0,)),
+                        ("k_combine<float>", 2, 3, (1, 2))],
+                "bf16": [("k_gather_sum<unsigned short, 8, 1, 4, 4, false>", 1, 1, (0,)),
+                         ("k_combine<unsigned short>", 1, 2, (1,))]},
+    "gemm1": {"f32": [("k_gemm_split<2, 8, 4,", 1, 1, (0,))],
+              "bf16": [("k_gemm_bres<2, 8, 3>", 1, 1, (0,))]},
+    "gemm2": {"f32": [("k_gemm_split<1, 3, 4,", 1, 1, (0,))],
+              "bf16": [("k_gemm<unsigned short, 2, 3,", 1, 1, (0,))]},
 }
+
+
+def _device_headers(name):
+    """The headers with device code (*_device.h) that a source file includes."""
+    out = set()
+    with open(os.path.join(PKG, "csrc", name)) as f:
+        for h in re.findall(r'#include "(\w+_device\.h)"', f.read()):
+            out |= {h} | _device_headers(h)
+    return out
+
+
+def kernel_sources(names):
+    """The source files of these kernels, sorted: the file that defines each and
+    its device headers.  A counter record is valid while their hash matches."""
+    defined = {}
+    for p in glob.glob(os.path.join(PKG, "csrc", "*.hip")):
+        with open(p) as f:
+            for k in re.findall(r"__global__[^;{]*?\b(k_\w+)\(", f.read()):
+                defined[k] = os.path.basename(p)
+    out = set()
+    for n in names:
+        src = defined[re.match(r"k_\w+", n).group()]
+        out |= {src} | _device_headers(src)
+    return sorted(out)
 
 
 def _short(name):
@@ -97,9 +116,12 @@ def _csv(d, suffix):
     return hits[0]
 
 
-def src_sha(name):
-    with open(os.path.join(PKG, "csrc", name), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def src_sha(names):
+    h = hashlib.sha256()
+    for name in names:
+        with open(os.path.join(PKG, "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def kernel_stats(trace_dir):
@@ -140,14 +162,6 @@ def calibration(acc, copy_mib):
         return None
     counted_kib = max(vals)
     return (copy_mib * 1024.0) / counted_kib if counted_kib > 0 else None
-
-
-# main kernel source of each suite stage (the traffic record is valid while
-# its hash matches)
-def _stage_source(stage):
-    if stage == "LSTM gather":
-        return "lstm.hip"
-    return "gather.hip" if "gather" in stage else "gemm.hip"
 
 
 def dispatches(counter_dir, counter):
@@ -281,6 +295,7 @@ def suite_main(a):
              f"{'workload':10s} {'layer':>5s} {'stage':28s} {'FETCH MB':>10s} {'WRITE MB':>10s}  kernels"]
     rec_path = os.path.join(a.out, "traffic.json")
     rec = json.load(open(rec_path)) if os.path.exists(rec_path) else {}
+    rec = {k: v for k, v in rec.items() if not k.startswith("suite:")}
     for key in sorted(fa, key=lambda k: (k[0], k[1])):
         wl, li, stage = key
         n = ncalls[wl]
@@ -288,7 +303,7 @@ def suite_main(a):
         wb = wa.get(key, 0.0) * cw * 1024 / n
         lines.append(f"{wl:10s} {li:5d} {stage:28s} {fb / 1e6:10.2f} {wb / 1e6:10.2f}  "
                      + ", ".join(sorted(k[:48] for k in fk[key])))
-        src = _stage_source(stage)
+        src = kernel_sources(fk[key])
         rec[f"suite:{wl}:L{li}:{stage}:f32"] = {
             "kernels": sorted(fk[key]), "source": src, "src_sha": src_sha(src),
             "bytes_per_launch": fb + wb, "fetch_bytes_per_launch": fb, "write_bytes_per_launch": wb,
@@ -340,7 +355,7 @@ def counters_main(a):
             if cname in names:
                 continue
             names.append(cname)
-            for stage, (pats, _src) in STAGES.items():
+            for stage, pats in STAGES.items():
                 total, ok = 0.0, True
                 for pat, per, cycle, slots in pats[a.dtype]:
                     keys = [k for k in by_kernel if k.startswith(pat)]
@@ -471,7 +486,8 @@ def main():
     rec_path = os.path.join(a.out, "traffic.json")
     rec = json.load(open(rec_path)) if os.path.exists(rec_path) else {}
     tr_us = trace_lists(a.trace)
-    for stage, (pats, src) in STAGES.items():
+    for stage, pats in STAGES.items():
+        src = kernel_sources(p[0] for p in pats[a.dtype])
         parts = []
         for pat, per, cycle, slots in pats[a.dtype]:
             keys = [k for k in set(fe) | set(wr) if k.startswith(pat)]

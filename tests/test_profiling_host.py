@@ -99,3 +99,27 @@ def test_marker_ranges_attributed_to_layer_calls_and_stages():
         P.attribute_ranges(sorted(bad, key=lambda x: (x[1], -x[2])), sched)
     with pytest.raises(ValueError):
         P.attribute_ranges(sorted(rng, key=lambda x: (x[1], -x[2]))[:-2], sched)
+
+
+def test_records_are_tied_to_the_files_their_kernels_are_in(tmp_path, monkeypatch):
+    """Every kernel name of the stage rules belongs to the file that defines it
+    and the device headers that file includes; a change in any of them changes
+    the hash a counter record carries."""
+    split = ["gemm_device.h", "gemm_split.hip", "saga_device.h"]
+    sources = lambda stage, dt: P.kernel_sources(p[0] for p in P.STAGES[stage][dt])  # noqa: E731
+    assert sources("gemm1", "f32") == sources("gemm2", "f32") == split
+    assert sources("gemm1", "bf16") == ["gemm.hip", "gemm_device.h", "saga_device.h"]
+    assert sources("gather1", "f32") == ["gather.hip", "saga_device.h"]
+    assert P.kernel_sources(["k_pack_split", "k_gru_split<4>"]) == split
+    assert "gemm_stream.hip" in P.kernel_sources(["k_gemm_stream<1, 13, 8>"])
+    with pytest.raises(KeyError):
+        P.kernel_sources(["k_gone"])
+    (tmp_path / "csrc").mkdir()
+    monkeypatch.setattr(P, "PKG", str(tmp_path))
+    seen = set()
+    for text in ("a", "b"):
+        for f in split:
+            (tmp_path / "csrc" / f).write_text("x")
+        (tmp_path / "csrc" / "gemm_device.h").write_text(text)
+        seen.add(P.src_sha(split))
+    assert len(seen) == 2
