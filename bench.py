@@ -474,7 +474,7 @@ def suite_stages(name, g, rel_counts=None):
     saga_trace_stages reports them in), with the algorithmic work of each:
     [[(stage, kind, bytes, flops), ...] per layer]; kind "mfma" for the
     dense transforms (priced against the float32 MFMA peak), "hbm" for the
-    Gathers."""
+    Gathers.  A stage with no work of its own has 0 bytes and 0 flops."""
     V, E = g["num_vertices"], g["num_edges"]
     G = lambda st, w: (st, "mfma", *w)  # noqa: E731
     A = lambda st, w: (st, "hbm", *w)   # noqa: E731
@@ -499,8 +499,9 @@ def suite_stages(name, g, rel_counts=None):
     if name == "gated_rgg":
         F, Fe = g["H"].shape[1], g["E_feat"].shape[1]
         gru_b = (2 * V * F + 2 * F * 3 * F + V * F) * 4
-        return [[G("source-gate transform", _gemm_work(V, F, F)),
-                 G("destination-gate transform", _gemm_work(V, F, F)),
+        # one product writes both gate operands; the second stage is empty
+        return [[G("source-gate transform", _gemm_work(V, F, 2 * F)),
+                 G("destination-gate transform", (0, 0)),
                  A("gated gather", _gather_work(V, E, F, F, per_edge_bytes=Fe * 4,
                                                 per_row_bytes=2 * F * 4,
                                                 flops_per_edge=2 * Fe * F + 8 * F)),
@@ -556,9 +557,12 @@ def suite_rooflines(name, stages, samples):
             t_ms = statistics.fmean(v)
             t = t_ms * 1e-3
             d = {"layer": li + 1, "stage": st, "bound": kind, "ms": round(t_ms, 5),
-                 "ms_spread": spread(v, 5),
-                 "compulsory_bytes": byts, "compulsory_GBps": byts / t / 1e9,
-                 "compulsory_frac_of_8TBps": byts / t / PEAK_HBM}
+                 "ms_spread": spread(v, 5), "compulsory_bytes": byts}
+            if byts == 0:  # nothing runs in it: no rates
+                out.append(d)
+                continue
+            d["compulsory_GBps"] = byts / t / 1e9
+            d["compulsory_frac_of_8TBps"] = byts / t / PEAK_HBM
             if kind == "mfma":
                 d["TFLOPs"] = flops / t / 1e12
                 d["mfma_frac"] = flops / t / PEAK_MFMA["f32"]
