@@ -650,20 +650,24 @@ hipError_t launch_bres(const GemmArgs& g, hipStream_t st) {
 }
 
 // The weight-resident kernel takes bfloat16 PLAIN products with 80 < N <= 128
-// (narrower outputs use the narrow tiles) and 256 <= K <= 608.  On 2^21 rows x
-// 128 columns against streamed weights (gemm_stream.hip): 0.353 / 0.362 ms at
-// K = 256, 0.454 / 0.477 at 384, 0.663 / 0.679 at 602 (two 16-row tiles per
-// wave, three A slots: as fast as four, which spill registers); below K = 256
-// the streamed weights win (K = 192: 0.333 / 0.320).
-bool takes_bres(int dtype, int mode, int64_t N, int64_t K) {
-  return dtype == SAGA_BF16 && mode == SAGA_GEMM_PLAIN && N > 80 && N <= 128 && K >= 256 &&
-         K <= 32 * kResHalfChunks;
+// (narrower outputs use the narrow tiles) and K up to 608: from K = 256 on
+// always, two 16-row tiles per wave and three A slots (2^21 rows x 128 columns
+// against streamed weights, gemm_stream.hip: 0.353 / 0.362 ms at K = 256, 0.454 /
+// 0.477 at 384, 0.663 / 0.679 at 602; four slots spill registers); from K = 192
+// on over many rows, one tile per wave and four slots (us, resident / streamed:
+// 500,000 x 208 x 128 81 / 89, x 240 x 96 85 / 89, x 192 x 128 79 / 83, but x 192 x
+// 96 74 / 79 the other way; 400,000 x 240 x 128 70 / 78, but x 192 x 128 67 / 61).
+bool takes_bres(int dtype, int mode, int64_t M, int64_t N, int64_t K) {
+  if (dtype != SAGA_BF16 || mode != SAGA_GEMM_PLAIN || N <= 80 || N > 128 || K > 32 * kResHalfChunks) return false;
+  if (K >= 256) return true;
+  return N > 112 ? K >= 192 && M >= (K >= 224 ? 350000 : 450000) : K > 192 && M >= 450000;
 }
 
 template <typename T>
 hipError_t dispatch(const GemmArgs& g, hipStream_t st) {
   if constexpr (sizeof(T) == 2)
-    if (takes_bres(g.dtype, g.mode, g.N, g.K)) return launch_bres<2, 8, 3>(g, st);
+    if (takes_bres(g.dtype, g.mode, g.M, g.N, g.K))
+      return g.K < 256 ? launch_bres<1, 8, 4>(g, st) : launch_bres<2, 8, 3>(g, st);
   const Tiling t = choose(g.dtype, g.mode, g.N, g.mode == SAGA_GEMM_CONCAT ? g.K + g.K2 : g.K);
   if constexpr (sizeof(T) == 2) {  // float32: gemm_split.hip
     if (g.mode == SAGA_GEMM_GRU) {
@@ -754,25 +758,56 @@ void grouped_packed(int dtype, int64_t N, int64_t K, int64_t* np, int64_t* kp) {
 
 }  // namespace
 
-// One k chunk an operand (K, K2 <= 64) and a concat or more than 208 columns:
-// the 128-column tiles, whose single step prefetches nothing, stay (578959 x
-// (31 + 31) x 250: 202 us, streamed 230; 575339 x (64 + 64) x 98: 91, 97; but
-// 300000 x 20 x 160: 59, 37).
-bool gemm_streams(int dtype, int mode, int64_t N, int64_t K, int64_t K2) {
-  if (dtype != SAGA_BF16 || mode == SAGA_GEMM_GRU || N <= 80 || takes_bres(dtype, mode, N, K)) return false;
+// Whether the 128-column tiles (eight waves, four stages) beat streamed weights.
+// With few k chunks their prefetch covers the whole product, and they waste little
+// where N is close below one or two tiles (times as tiles / streamed):
+//  - 113 to 128 columns, one operand, K < 192: with whole chunks from 24,000 rows
+//    (60,000 x 128 x 128 13.1 / 14.7 us, 600,000 x 64 x 128 52 / 58; 20,000 rows
+//    1.03 to 1.10), else where the streamed workgroups of 64 rows come to an
+//    unlucky number of rounds (K = 20 to 176: 0.90 to 0.97 at 50,000 and 65,000
+//    rows, 0.93 to 0.99 at 400,000, but 1.00 to 1.06 at 80,000 to 250,000 and 0.96
+//    to 1.07 past 800,000); two operands of whole chunks, up to four in all, over
+//    many rows (128 + 128: 0.95 at 400,000 rows, 1.02 at 300,000)
+//  - two tiles over few rows, where the streamed column blocks are cut to seven
+//    tiles (up to four chunks, 256 columns: 0.82 to 0.95 at 9,000 to 25,000 rows;
+//    one operand, K <= 128, 208 columns: 0.90 to 0.98)
+//  - 177 to 207 columns, one operand, whose single streamed block of 12 or 13
+//    tiles leaves few waves in flight (200 columns, 50,000 / 130,000 rows: K = 64
+//    0.83 / 0.94, K = 128 0.88 / 0.97, K = 192 0.91 / 1.02, K = 256 0.96 / 1.11);
+//    209 to 256, two whole chunks (240 columns, 65,000 rows 0.94, 130,000 0.90 on
+//    new inputs each call, 1.00 on the same)
+bool tiles_win(int mode, int64_t M, int64_t N, int64_t K, int64_t K2) {
+  const bool plain = mode == SAGA_GEMM_PLAIN, whole = K % 64 == 0 && K2 % 64 == 0;
+  const int64_t ch = (K + 63) / 64 + (K2 + 63) / 64;
+  if (N > 112 && N <= 128) {
+    if (!plain) return whole && ch <= 4 && M >= 400000;
+    return K < 192 && (whole ? M >= 24000 : (M >= 40000 && M < 75000) || (M >= 300000 && M < 700000));
+  }
+  if (M < 32768) return M >= 9000 && ((N > 240 && N <= 256 && ch <= 4) || (plain && N > 192 && N <= 208 && K <= 128));
+  if (!plain || M < 40000 || M >= (K <= 128 ? 150000 : 75000)) return false;
+  return (N > 176 && N < 208 && K <= 192) || (N > 208 && N <= 256 && K == 128);
+}
+
+// Whether a product streams its weights.  One k chunk an operand (K, K2 <= 64) and
+// a concat or more than 208 columns: the tiles, whose single step prefetches
+// nothing, stay (578959 x (31 + 31) x 250: 202 us, streamed 230; 575339 x (64 +
+// 64) x 98: 91, 97; but 300000 x 20 x 160: 59, 37).  M < 0: for some M.
+bool gemm_streams(int dtype, int mode, int64_t M, int64_t N, int64_t K, int64_t K2) {
+  if (dtype != SAGA_BF16 || mode == SAGA_GEMM_GRU || N <= 80 || takes_bres(dtype, mode, M, N, K)) return false;
+  if (tiles_win(mode, M, N, K, K2)) return false;
   return K > 64 || K2 > 64 || (mode == SAGA_GEMM_PLAIN && N <= 208);
 }
 
 size_t gemm_workspace_bytes(int dtype, int mode, int64_t N, int64_t K, int64_t K2) {
   if (mode != SAGA_GEMM_CONCAT && mode != SAGA_GEMM_GRU) K2 = 0;
-  if (gemm_streams(dtype, mode, N, K, K2)) return stream_workspace_bytes(N, K, K2);
   if (gemm_splits(dtype, mode, N, K + K2)) return split_workspace_bytes(mode, N, K, K2, 1);
-  return packed_layout(dtype, mode, N, K, K2).bytes;
+  const size_t packed = packed_layout(dtype, mode, N, K, K2).bytes;
+  return gemm_streams(dtype, mode, -1, N, K, K2) ? std::max(packed, stream_workspace_bytes(N, K, K2)) : packed;
 }
 
 hipError_t launch_gemm(const GemmArgs& g0, hipStream_t st) {
   if (g0.M == 0) return hipSuccess;
-  if (gemm_streams(g0.dtype, g0.mode, g0.N, g0.K, g0.mode == SAGA_GEMM_PLAIN ? 0 : g0.K2))
+  if (gemm_streams(g0.dtype, g0.mode, g0.M, g0.N, g0.K, g0.mode == SAGA_GEMM_PLAIN ? 0 : g0.K2))
     return launch_gemm_stream(g0, st);
   if (g0.forms() || gemm_splits(g0.dtype, g0.mode, g0.N, g0.K + (g0.mode == SAGA_GEMM_CONCAT ? g0.K2 : 0)))
     return launch_gemm_split(g0, st);

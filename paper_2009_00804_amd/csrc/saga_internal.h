@@ -187,7 +187,7 @@ size_t gemm_grouped_workspace_bytes(int dtype, int groups, int64_t N, int64_t K)
 hipError_t launch_gemm_grouped(const GemmArgs& g, hipStream_t st);
 
 // ---- gemm_stream.hip: bfloat16 PLAIN / CONCAT with more than 80 columns ----
-bool gemm_streams(int dtype, int mode, int64_t N, int64_t K, int64_t K2);
+bool gemm_streams(int dtype, int mode, int64_t M, int64_t N, int64_t K, int64_t K2);
 size_t stream_workspace_bytes(int64_t N, int64_t K, int64_t K2);
 hipError_t launch_gemm_stream(const GemmArgs& g, hipStream_t st);
 

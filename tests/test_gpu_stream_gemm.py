@@ -73,3 +73,39 @@ def test_products_of_many_rows(M, K, K2, N):
     ref = sum(_bf(x[rows]) @ _bf(y) for x, y in zip(a, w))
     mag = sum(np.abs(_bf(x[rows])) @ np.abs(_bf(y)) for x, y in zip(a, w))
     assert np.all(np.abs(got - ref) <= (K + K2 + 2) * 2.0 ** -24 * mag + 2.0 ** -8 * np.abs(ref) + 1e-30)
+
+
+@pytest.mark.parametrize("M,K,K2,N", [
+    (23999, 64, 0, 128), (24000, 64, 0, 128), (39999, 100, 0, 113), (40000, 100, 0, 113), (74999, 191, 0, 128),
+    (75000, 191, 0, 128), (100000, 128, 0, 120), (299999, 72, 0, 128), (300000, 72, 0, 128), (699999, 20, 0, 128),
+    (700000, 20, 0, 128), (349999, 224, 0, 128), (350000, 224, 0, 128), (449999, 193, 0, 96), (450000, 193, 0, 96),
+    (450000, 192, 0, 112), (450003, 192, 0, 128), (450000, 255, 0, 81), (8999, 70, 0, 256), (9000, 70, 0, 256),
+    (12001, 128, 128, 250), (32767, 100, 0, 208), (32768, 100, 0, 208), (39999, 128, 0, 200), (40000, 128, 0, 200),
+    (149999, 65, 0, 180), (150000, 65, 0, 180), (74999, 192, 0, 207), (75000, 192, 0, 207), (399999, 64, 128, 120),
+    (400000, 64, 128, 120), (65001, 128, 0, 209)])
+def test_lines_between_the_kernels(M, K, K2, N):
+    """Both sides of where streamed weights, 128-column tiles and resident weights
+    take over from each other; a workspace of the size asked for serves all."""
+    g = torch.Generator(device=DEV).manual_seed(M + K + K2 + N)
+
+    def rows16(k):
+        a = torch.randn(M, (k + 7) // 8 * 8, generator=g, device=DEV).to(torch.bfloat16)
+        a[:, k:] = float("nan")
+        return a[:, :k]
+
+    a = [rows16(k) for k in (K, K2) if k]
+    w = [(torch.rand(k, N, generator=g, device=DEV) * 2 - 1).to(torch.bfloat16) for k in (K, K2) if k]
+    op = S.saga_gemm_op()
+    op.dtype, op.mode = S.SAGA_BF16, S.SAGA_GEMM_CONCAT if K2 else S.SAGA_GEMM_PLAIN
+    out = S.padded_empty(M, N, torch.bfloat16, DEV)
+    out.fill_(float("nan"))
+    ws = S.workspace(S.saga_apply_vertex_workspace_size(op, K, K2, N), DEV)
+    print(f"lines {M} x {K}+{K2} x {N}", flush=True)
+    S.saga_apply_vertex(op, S.cmat(a[0]), S.cmat(w[0]), S.cmat(a[1] if K2 else None), S.cmat(w[1] if K2 else None),
+                        None, None, S.mat(out), S._ptr(ws), ws.numel(), S.stream_handle())
+    assert not bool(torch.isnan(out).any())
+    rows = torch.cat([torch.arange(130), torch.randint(M, (800,)), torch.arange(M - 130, M)]).to(DEV)
+    got = to_np(out[rows])
+    ref = sum(to_np(x[rows]) @ to_np(y) for x, y in zip(a, w))
+    mag = sum(np.abs(to_np(x[rows])) @ np.abs(to_np(y)) for x, y in zip(a, w))
+    assert np.all(np.abs(got - ref) <= (K + K2 + 2) * 2.0 ** -24 * mag + 2.0 ** -8 * np.abs(ref) + 1e-30)
