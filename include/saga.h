@@ -534,6 +534,12 @@ saga_status saga_lstm_gather_rows(const saga_plan* plan, int32_t perm_begin, int
  * a: M x K, w: K x N (dense weights, ld may exceed N), out: M x N; bf16 or
  * f32 storage per op->dtype, float32 accumulation; N <= 4096 per call.
  *
+ * float32 products of more than 32 columns or 256 k run on the bfloat16 matrix
+ * cores, every operand as an exact sum of three bfloat16 values, with the
+ * accuracy of float32 sums.  Rows that reach 2^110, or whose magnitude times
+ * that of the weights times (k + k2) reaches 2^94, infinities included, are
+ * computed by a path about four times slower.
+ *
  * Workspace: device memory of at least saga_apply_vertex_workspace_size()
  * bytes, 256-byte aligned, owned by the caller and not overlapping any
  * argument.  Each call first writes w (and w2) into it transposed and

@@ -20,6 +20,12 @@ namespace {
 // them take 3/8 of its time.  Up to four k the rest is not small beside the sum's own
 // rounding; such a product, which memory bounds, takes all nine terms.
 //
+// What bounds it: the matrix cores.  2^21 x 602 x 128 takes 1.81 ms (float32
+// instruction 2.89), 1,085 TFLOP/s of bfloat16 products where an 8192^3 product
+// reaches 1,202; with one accumulator the products alone took 1.15 ms at the 1.87
+// GHz the power limit leaves under this load, the A loads added 0.35, the weights
+// 0.27, the stores 0.14.
+//
 // Accumulation.  The instruction adds its 32 products to the accumulator eight
 // at a time and rounds after each eight, v_mfma_f32_16x16x4f32 after each
 // product.  a1 w1 has accumulators of its own, the five small terms (2^-8 of it)
@@ -643,12 +649,12 @@ hipError_t launch_split(const GemmArgs& g, int ny, hipStream_t st) {
 
 // Tile shape, measured (us, float32 matrix instructions / 32 rows per wave /
 // 16 rows per wave; four waves): long K over many rows takes 32 rows a wave,
-// which halves the LDS reads per product (2^21 x 602 x 128: 2918 / 1867 / 1942;
-// 131072 x 512 x 256 in two operands: 316 / 201 / 218; 600000 x 300 x 300:
-// 1441 / 751 / 772).  Up to seven k chunks, or too few tiles to fill the chip
-// twice over, 16 rows: more waves in flight (100000 x 64 x 64: 22.0 / 21.6 /
-// 19.1; 500000 x 100 x 48: 91 / 90 / 78; 5000 x 602 x 256: 53 / 35 / 26;
-// 20000 x 512 x 80: 35 / 26 / 24).
+// which halves the LDS reads per product (2^21 x 602 x 128: 2888 / 1806 / 1949;
+// 131072 x 512 x 256 in two operands: 312 / 185 / 196; 600000 x 300 x 300: 1411 /
+// 722 / 734).  Up to seven k chunks, or too few tiles to fill the chip twice over,
+// 16 rows: more waves in flight (100000 x 64 x 64: 20.2 / 20.9 / 18.2; 500000 x
+// 100 x 48: 90.9 / 75.9 / 76.9; 5000 x 602 x 256: 51.9 / 32.2 / 23.8; 20000 x 512 x
+// 80: 33.7 / 24.8 / 22.5).
 template <int NT, bool GROUPED>
 hipError_t dispatch_split_nt(const GemmArgs& g, const SplitShape& s, int64_t chunks, hipStream_t st) {
   const bool tall = chunks >= 8 && (GROUPED || (g.M + 127) / 128 * s.ny >= 1024);

@@ -1,9 +1,9 @@
 // ApplyVertex in bfloat16, PLAIN and CONCAT with more than 80 columns: all
-// columns of a row block (up to 208) in one workgroup, so that A is read once.
-// Measured (us, against 128-column tiles with swizzled weights): 232965 x (300 +
-// 300) x 200 199 -> 135, 600000 x 300 x 300 428 -> 273, 600000 x 128 x 96 83 ->
-// 61, 2^21 x 192 x 128 333 -> 320 (against resident weights).  The loads are
-// what it waits for: 2.6 to 4.5 TB/s of the bytes it cannot do without.
+// columns of a row block (up to 208) in one workgroup, so that A is read once
+// (which products take it: gemm_streams).  Measured (us, against 128-column tiles
+// with swizzled weights): 232965 x (300 + 300) x 200 199 -> 122, 600000 x 300 x 300
+// 402 -> 266, 600000 x 128 x 96 72 -> 58.  Loads bound it: 2.7 to 4.5 TB/s of the
+// bytes it cannot do without.
 #include <algorithm>
 
 #include "gemm_device.h"
@@ -20,11 +20,12 @@ typedef __attribute__((address_space(3))) uint4 lds_uint4;
 // free of bank conflicts.
 //
 // At the top of step i the weights of chunk i + 1 start on their way into the
-// other stage and the A rows of chunk i + 2 into the registers chunk i
-// leaves.  The
-// direct-to-LDS loads are written in assembly: the compiler would otherwise
+// other stage and the A rows of chunk i + 2 into the registers chunk i leaves.
+// The direct-to-LDS loads are written in assembly: the compiler would otherwise
 // wait for every one in flight before any LDS read.  Loads return in order, so
 // waiting until only the newest chunk's A loads are pending covers the weights.
+// As built, the loop moves registers of pending A loads at its end, so every
+// second step first waits for all loads in flight.
 template <int MT, int NT, int NW>
 struct Stream {
   typedef uint16_t T;
@@ -214,10 +215,14 @@ __global__ __launch_bounds__(kThreads) void k_pack_stream(PackIn i1, PackIn i2, 
 }
 
 // Column blocks of nt 16-column tiles, of equal width.  One block up to 13
-// tiles (232965 x 600 x 200: 125 us, two blocks 140); past that blocks of at
-// most ten (66211 x 524 x 250, 16 tiles: one block 68, two 47 to 49; 600000 x
-// 300 x 300, 19 tiles: two blocks 274, three 297).  Over few rows blocks of at
-// most seven, for more workgroups (13864 x 55 x 196, tanh: 18 -> 15).
+// tiles: with long K or many rows it saves the second read of A (us, one block /
+// two: 232965 x (300 + 300) x 140 109 / 132, x 170 115 / 135, x 200 122 / 140;
+// 600000 x 300 x 190 187 / 206), but 9, 11 and 12 tiles of one short operand over
+// fewer rows lose some of it (232965 x 300 x 190 75 / 63, 100000 x 72 x 170 29 /
+// 24; x 160 20 / 20).  Past that blocks of at most ten (66211 x 524 x 250, 16
+// tiles: one block 68, two 44 to 49; 600000 x 300 x 300, 19 tiles: two blocks 266,
+// three 297).  Over few rows blocks of at most seven, for more workgroups (13864 x
+// 55 x 196, tanh: 18 -> 15; 40000 x 72 x 190 17.4 / 15.1).
 constexpr int64_t kFewRows = 32768;
 struct StreamShape {
   int nt, ny;
@@ -245,7 +250,9 @@ hipError_t launch_stream(const GemmArgs& g, int ny, hipStream_t st) {
 // reads per product (600000 x 256 x 128: 116 us, 121 with 16; 131072 x 512 x
 // 256: 68, 74), else 16 (111353 x 173 x 119: 28, 34; 197125 x 345 x 236: 79,
 // 83).  More: their accumulators leave room for 16 rows, and over many rows
-// eight waves share the weights (232965 x 600 x 200: 135, four waves 143).
+// eight waves share the weights (us, eight / four: 600000 x (300 + 300) x 140 250 /
+// 266, x 200 287 / 304, 232965 x (300 + 300) x 200 125 / 125, but one short operand
+// at 131072 to 250000 rows 232965 x 300 x 160 58 / 51).
 template <int NT>
 hipError_t dispatch_stream(const GemmArgs& g, int ny, hipStream_t st) {
   if constexpr (NT > 8) {

@@ -36,7 +36,7 @@
 //     load is issued, with scalar addresses, before its multiply-adds and not
 //     at the end of the step, where every wave would wait for it at the barrier.
 // Measured, GraphSAGE-LSTM layer at 131,072 vertices, H = 128, longest row about
-// 19,800 in-edges (ms): groups of 4 lanes 12.35, 8 12.18, 16 12.74; before, with
+// 19,800 in-edges (ms): groups of 4 lanes 12.35, 8 12.18 (12.0 as built now), 16 12.74; before, with
 // groups of 4, selects in the exchange, the loads at the end of a step and a
 // chain of scalar branches around every wait, 15.70.  One column a lane with h
 // broadcast by a DPP modifier on every multiply-add reads the least LDS but took
